@@ -10,6 +10,7 @@
 
 #include <cmath>
 
+#include "m1_device.h"
 #include "m1_internal.h"
 
 namespace fm1 {
@@ -42,69 +43,118 @@ struct MatterArgs {
   double c, dt;
 };
 
-// x^3 / (e^x - 1) integrated from 0 to x (x below the split), from the expansion of
-// x / (e^x - 1) in Bernoulli numbers: x^3 (1/3 - x/8 + sum_j b_j x^(2j)),
-// b_j = B_2j / ((2j)! (2j + 3)), summed by Horner's rule in x^2.
+// 1/x and sqrt(x) of normal positive arguments to about an ulp: the hardware estimates refined
+// by two Newton-Raphson steps (the library division and square root spend twice the
+// instructions on scaling and on the last half ulp).
+__device__ __forceinline__ double rcp2(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+
+// a b + c with the constant c held in scalar registers: a Horner step is then one instruction (the
+// compiler copies a constant addend into vector registers first, one move per step).  a and b
+// never come straight from a transcendental instruction.
+__device__ __forceinline__ double fma_c(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
+// e^(-x) and e^(-x) - 1 for 0 <= x <= EXP_MAX: x = -n ln 2 - r with |r| <= ln(2)/2 (ln 2 in two
+// parts, the first of 42 bits so that n times it is exact), e^r - 1 by its Taylor series through
+// r^13 (the next term is below 5e-18 there), scaled by 2^n.  e^(-EXP_MAX) underflows to 0.
+constexpr double EXP_MAX = 800.0;
+__device__ __forceinline__ void exp_neg(double x, double& q, double& em) {
+  const double n = rint(x * -1.4426950408889634);
+  const double r = fma(n, -0x1.ef35793c7673p-45, fma(n, -0x1.62e42fefa38p-1, -x));
+  double p = 1.0 / 6227020800.0;
+  p = fma_c(p, r, 1.0 / 479001600.0);
+  p = fma_c(p, r, 1.0 / 39916800.0);
+  p = fma_c(p, r, 1.0 / 3628800.0);
+  p = fma_c(p, r, 1.0 / 362880.0);
+  p = fma_c(p, r, 1.0 / 40320.0);
+  p = fma_c(p, r, 1.0 / 5040.0);
+  p = fma_c(p, r, 1.0 / 720.0);
+  p = fma_c(p, r, 1.0 / 120.0);
+  p = fma_c(p, r, 1.0 / 24.0);
+  p = fma_c(p, r, 1.0 / 6.0);
+  p = fma_c(p, r, 0.5);
+  const double e = fma(r * r, p, r);
+  const int k = (int)n;
+  const double s = ldexp(1.0, k);
+  q = ldexp(1.0 + e, k);
+  em = fma(s, e, s - 1.0);
+}
+
+// The Planck integrals int x^3 / (e^x - 1) dx of one group edge: from 0 below the split, to
+// infinity from the split on.  The split lies where the two are about equal, which makes the
+// worst cancellation between a group's two edge values smallest, and both series are short and
+// of fixed length: 14 coefficients below it, four sums of PLANCK_N terms above it (a split at 1.5,
+// where 12 Bernoulli terms suffice, needs 26 terms above it).
+constexpr double PLANCK_SPLIT = 3.5;
+constexpr int PLANCK_N = 10;   // e^(-3.5 n) terms left out: 3e-17 of the integral at the split
+// int_0^split and int_split^inf (their sum is pi^4/15)
+constexpr double PLANCK_HS = 3.242940546215698, PLANCK_HH = 3.250998856051131;
+// sum_{j >= 1} B_2j / ((2j)! (2j + 3)) y^(j-1), the even part of the expansion
+// int_0^x = x^3 (1/3 - x/8 + sum_j B_2j/((2j)! (2j+3)) x^(2j)), as the polynomial in y = x^2 that
+// interpolates it at the 14 Chebyshev points of [0, split^2] (4e-18 of the integral), highest
+// power first
+constexpr double c_low[14] = {
+    -4.579610424450894e-25,  5.874799171410437e-23,  -4.006866021371855e-21, 2.0518102281657752e-19,
+    -9.313783042183928e-18,  4.0790272619149505e-16, -1.7835812091183352e-14, 7.871924029860963e-13,
+    -3.522789804744265e-11,  1.605904329043872e-09,  -7.51563251067359e-08,   3.674309229841219e-06,
+    -0.000198412698412694,   0.016666666666666666};
+
 __device__ __forceinline__ double planck_low(double x) {
   const double y = x * x;
-  double p = -236364091.0 / (1693824136731743669452800000.0 * 27.0);
-  p = p * y + 77683.0 / (14101100039391805440000.0 * 25.0);
-  p = p * y - 174611.0 / (802857662698291200000.0 * 23.0);
-  p = p * y + 43867.0 / (5109094217170944000.0 * 21.0);
-  p = p * y - 3617.0 / (10670622842880000.0 * 19.0);
-  p = p * y + 1.0 / (74724249600.0 * 17.0);
-  p = p * y - 691.0 / (1307674368000.0 * 15.0);
-  p = p * y + 1.0 / (47900160.0 * 13.0);
-  p = p * y - 1.0 / (1209600.0 * 11.0);
-  p = p * y + 1.0 / (30240.0 * 9.0);
-  p = p * y - 1.0 / (720.0 * 7.0);
-  p = p * y + 1.0 / (12.0 * 5.0);
-  return x * y * (1.0 / 3.0 - x * 0.125 + y * p);
+  double p = c_low[0];
+#pragma unroll
+  for (int k = 1; k < 14; ++k) p = fma_c(p, y, c_low[k]);
+  return x * y * fma(y, p, fma(x, -0.125, 1.0 / 3.0));
 }
 
-// 1/n for the terms of the exponential series
-__constant__ double c_recip[64] = {
-    1.0,        1.0 / 2,  1.0 / 3,  1.0 / 4,  1.0 / 5,  1.0 / 6,  1.0 / 7,  1.0 / 8,  1.0 / 9,  1.0 / 10, 1.0 / 11,
-    1.0 / 12,   1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16, 1.0 / 17, 1.0 / 18, 1.0 / 19, 1.0 / 20, 1.0 / 21, 1.0 / 22,
-    1.0 / 23,   1.0 / 24, 1.0 / 25, 1.0 / 26, 1.0 / 27, 1.0 / 28, 1.0 / 29, 1.0 / 30, 1.0 / 31, 1.0 / 32, 1.0 / 33,
-    1.0 / 34,   1.0 / 35, 1.0 / 36, 1.0 / 37, 1.0 / 38, 1.0 / 39, 1.0 / 40, 1.0 / 41, 1.0 / 42, 1.0 / 43, 1.0 / 44,
-    1.0 / 45,   1.0 / 46, 1.0 / 47, 1.0 / 48, 1.0 / 49, 1.0 / 50, 1.0 / 51, 1.0 / 52, 1.0 / 53, 1.0 / 54, 1.0 / 55,
-    1.0 / 56,   1.0 / 57, 1.0 / 58, 1.0 / 59, 1.0 / 60, 1.0 / 61, 1.0 / 62, 1.0 / 63, 1.0 / 64};
-
-// x^3 / (e^x - 1) integrated from x to infinity (x at or above the split; +inf gives 0):
-// sum over n of the closed-form integral of x^3 e^(-n x), the powers e^(-n x) by products.
-__device__ __forceinline__ double planck_high(double x) {
-  if (!(x < INFINITY)) return 0.0;
-  const double q = exp(-x);
-  const double x2 = x * x, x3 = x2 * x;
-  double qn = 1.0, s = 0.0;
-  for (int n = 0; n < 64; ++n) {
-    qn *= q;
-    const double r = c_recip[n];
-    const double term = qn * r * (x3 + r * (3.0 * x2 + r * (6.0 * x + 6.0 * r)));
-    s += term;
-    if (term <= 1e-18 * s) break;
+// sum over n of int_x^inf x^3 e^(-n x) = x^3 q^n/n + 3 x^2 q^n/n^2 + 6 x q^n/n^3 + 6 q^n/n^4,
+// q = e^(-x): four polynomials in q, each by Horner's rule (independent chains)
+__device__ __forceinline__ double planck_high(double x, double q) {
+  constexpr double N = PLANCK_N;
+  double a = 1.0 / N, b = 1.0 / (N * N), c = 1.0 / (N * N * N), d = 1.0 / (N * N * N * N);
+#pragma unroll
+  for (int n = PLANCK_N - 1; n >= 1; --n) {
+    const double m = n;
+    a = fma_c(a, q, 1.0 / m);
+    b = fma_c(b, q, 1.0 / (m * m));
+    c = fma_c(c, q, 1.0 / (m * m * m));
+    d = fma_c(d, q, 1.0 / (m * m * m * m));
   }
-  return s;
+  return q * fma(x, fma(x, fma(x, a, 3.0 * b), 6.0 * c), 6.0 * d);
 }
 
-constexpr double PLANCK_SPLIT = 1.5;
-
-// one edge's value in the form the group integrals need: the integral from 0 below the
-// split, the integral to infinity from the split on
-__device__ __forceinline__ double planck_edge(double x) { return x < PLANCK_SPLIT ? planck_low(x) : planck_high(x); }
-
-// integral of x^3 / (e^x - 1) over [a, b] (0 <= a <= b <= inf) from the edge values va, vb
-// (planck_edge), without subtracting two nearly equal integrals; hs = planck_low(split),
-// hh = planck_high(split)
-__device__ __forceinline__ double planck_part_v(double a, double b, double va, double vb, double hs, double hh) {
-  if (b < PLANCK_SPLIT) return vb - va;
-  if (a >= PLANCK_SPLIT) return va - vb;
-  return (hs - va) + (hh - vb);
+// one edge's value at x[0] and, with P = 2, at a nearby x[1] (relatively 1e-7 apart) in the same
+// form: the integral over [x[1], x[0]] by the midpoint rule (its error, the cube of the width, is
+// far below rounding)
+template <int P>
+__device__ __forceinline__ void planck_edge(const double* x, double* v) {
+  const double xc = fmin(x[0], EXP_MAX);
+  double q, em;
+  exp_neg(xc, q, em);
+  const bool low = x[0] < PLANCK_SPLIT;
+  if (low) v[0] = planck_low(xc);
+  else v[0] = planck_high(xc, q);
+  if constexpr (P == 2) {
+    // x^3 / (e^x - 1) at the midpoint, from e^(-x) there (x = 0: 0)
+    const double w = xc - fmin(x[1], EXP_MAX), u = 0.5 * w;
+    const double m = xc - u;
+    const double e = fma(q, u * fma(u, 0.5, 1.0), em);   // e^(-m) - 1
+    const double f = w * (m * m * m) * (1.0 + e) * rcp2(xc > 0.0 ? -e : 1.0);
+    v[1] = low ? v[0] - f : v[0] + f;
+  }
 }
 
-__device__ __forceinline__ double planck_part(double a, double b, double hs, double hh) {
-  return planck_part_v(a, b, planck_edge(a), planck_edge(b), hs, hh);
+// integral over a group from the values va, vb of its edges, each from 0 (its flag set) or to
+// infinity, without subtracting two nearly equal integrals
+__device__ __forceinline__ double planck_part(bool a_low, bool b_low, double va, double vb) {
+  return b_low ? vb - va : (a_low ? (PLANCK_HS - va) + (PLANCK_HH - vb) : va - vb);
 }
 
 // the value v of the lane whose byte address (4 x lane) is addr
@@ -115,30 +165,122 @@ __device__ __forceinline__ double lane_value(int addr, double v) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// sum of v over the 2^lg lanes of a zone
+template <int CTRL>
+__device__ __forceinline__ double row_dpp(double v) {
+  return __builtin_amdgcn_update_dpp(0.0, v, CTRL, 0xf, 0xf, true);
+}
+
+// v of the next lane (a zone's last lane does not use it): a row shift where zones lie inside
+// 16-lane rows, through LDS otherwise
+__device__ __forceinline__ double next_lane(double v, int lg) {
+  if (lg <= 4) return row_dpp<0x101>(v);
+  return lane_value((((int)threadIdx.x + 1) & 63) << 2, v);
+}
+
+// sum of v over the 2^lg lanes of a zone, in every lane: butterfly order; inside a 16-lane row
+// by lane permutations of the VALU (neighbour pairs, pairs of pairs, mirrored halves and rows:
+// the lanes of a pair or a half hold equal sums by then)
 __device__ __forceinline__ double zone_sum(double v, int lg) {
-  for (int o = 1; o < (1 << lg); o <<= 1) v += __shfl_xor(v, o);
+  if (lg >= 1) v += row_dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+  if (lg >= 2) v += row_dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  if (lg >= 3) v += row_dpp<0x141>(v);   // row_half_mirror
+  if (lg >= 4) v += row_dpp<0x140>(v);   // row_mirror
+  if (lg >= 5) v += __shfl_xor(v, 16);
+  if (lg >= 6) v += __shfl_xor(v, 32);
   return v;
 }
 
+// A lane's group: opacity and emission at P nearby temperatures (T[1] = T[0] (1 + 1e-7)).  A
+// lane evaluates the Planck integral at its group's lower edge and takes the upper edge's value
+// from the next lane; a zone's last lane, when it holds a group, evaluates the top edge itself
+// (lanes past the last group evaluate the top edge).  All lanes of a zone call together.
+struct GroupLane {
+  double nuc, nlo, nhi, pnorm;
+  double ntop;       // the top edge where the zone's last lane holds a group, else infinite
+  bool last;         // the zone's last lane
+  int lg;
+  __device__ __forceinline__ GroupLane(const MatterTab& tab, int G, int g, int lg_) : lg(lg_) {
+    const int gg = g < G ? g : 0;
+    nuc = tab.nu_c[gg];
+    nlo = tab.nu_edge[g < G ? g : G];
+    nhi = tab.nu_edge[gg + 1];
+    last = g == (1 << lg) - 1;
+    ntop = G == (1 << lg) ? tab.nu_edge[G] : INFINITY;
+    pnorm = tab.a_rad * 15.0 / (M_PI * M_PI * M_PI * M_PI);
+  }
+  template <int P>
+  __device__ __forceinline__ void at(const double* T, double kq, double* kap, double* B) const {
+    double iT[P], is[P], xa[P], va[P], vb[P];
+    iT[0] = rcp2(T[0]);
+    is[0] = sqrt_(iT[0]);
+    if constexpr (P == 2) {
+      // 1/T' and 1/sqrt(T') from those of T by the binomial series in (T' - T)/T
+      const double e = (T[1] - T[0]) * iT[0];
+      iT[1] = fma(iT[0], e * (e - 1.0), iT[0]);
+      is[1] = fma(is[0], e * fma(e, 0.375, -0.5), is[0]);
+    }
+    {
+      double qa, em;
+      const double a = fmin(nuc * iT[0], EXP_MAX);
+      exp_neg(a, qa, em);
+      kap[0] = kq * is[0] * -em;
+      if constexpr (P == 2) {
+        // e^(-a') - 1 = (e^(-a) - 1) + e^(-a) (e^u - 1), u = a - a' small
+        const double u = a - fmin(nuc * iT[1], EXP_MAX);
+        const double e1 = fma(qa, u * fma(u, fma(u, 1.0 / 6.0, 0.5), 1.0), em);
+        kap[1] = kq * is[1] * -e1;
+      }
+    }
+    for (int p = 0; p < P; ++p) xa[p] = nlo * iT[p];
+    planck_edge<P>(xa, va);
+    for (int p = 0; p < P; ++p) vb[p] = next_lane(va[p], lg);
+    if (ntop < INFINITY) {
+      if (last) {
+        double xt[P];
+        for (int p = 0; p < P; ++p) xt[p] = ntop * iT[p];
+        planck_edge<P>(xt, vb);
+      }
+    } else if (last) {
+      for (int p = 0; p < P; ++p) vb[p] = 0.0;
+    }
+    const bool al = xa[0] < PLANCK_SPLIT, bl = nhi * iT[0] < PLANCK_SPLIT;
+    for (int p = 0; p < P; ++p) {
+      const double T2 = T[p] * T[p];
+      B[p] = pnorm * (T2 * T2) * planck_part(al, bl, va[p], vb[p]);
+    }
+  }
+};
+
+// One lane per zone-group, a zone's groups on consecutive lanes (as k_matter_source): each lane
+// evaluates one edge instead of its group's two.  512^2 x 16 in double: 32 us
+// (143 us with both edges per lane, library exponentials and data-dependent series lengths)
 template <typename S>
 __global__ void __launch_bounds__(MBLOCK) k_matter_coeffs(MatterArgs<S> a, S* kap_out, S* B_out) {
-  const int64_t i = (int64_t)blockIdx.x * MBLOCK + threadIdx.x;
-  if (i >= a.nzones * a.G) return;
-  const int64_t z = i / a.G;
-  const int g = (int)(i - z * a.G);
+  const int64_t gt = (int64_t)blockIdx.x * MBLOCK + threadIdx.x;
+  const int64_t z = gt >> a.lg;
+  const int g = (int)(gt & ((1 << a.lg) - 1));
+  if (z >= a.nzones) return;   // whole zones leave together
+  const GroupLane gr(a.tab, a.G, g, a.lg);
+  const bool on = g < a.G;
   const double T = a.T[z];
-  const double hs = planck_low(PLANCK_SPLIT), hh = planck_high(PLANCK_SPLIT);
-  const double kap = a.kappa0[z] * a.tab.kg[g] / sqrt(T) * -expm1(-a.tab.nu_c[g] / T);
-  const double T2 = T * T;
-  const double B = a.tab.a_rad * T2 * T2 * (15.0 / (M_PI * M_PI * M_PI * M_PI)) *
-                   planck_part(a.tab.nu_edge[g] / T, a.tab.nu_edge[g + 1] / T, hs, hh);
-  kap_out[i] = (S)kap;
-  B_out[i] = (S)B;
+  double kap, B;
+  gr.at<1>(&T, a.kappa0[z] * a.tab.kg[on ? g : 0], &kap, &B);
+  if (on) {
+    const int64_t i = z * a.G + g;
+    kap_out[i] = (S)kap;
+    B_out[i] = (S)B;
+  }
 }
 
+// The interaction update with the outer solve.  Bound by double-precision VALU work (the bytes
+// take a tenth of its time), so the work per residual is what counts: the residual and its
+// forward-difference neighbour are evaluated together (every accepted temperature needs both),
+// sharing the exponentials, and the group sums are lane permutations instead of LDS round
+// trips.  512^2 x 16 in double, 3.1 iterations in the slowest zone of a wave: 242 us (821 us with
+// separate residuals, library exponentials and series of data-dependent length); VALU issue about
+// 60 % of the cycles at five waves per SIMD.
 template <typename S>
-__global__ void __launch_bounds__(MBLOCK) k_matter_source(MatterArgs<S> a) {
+__global__ void __launch_bounds__(MBLOCK) __attribute__((amdgpu_waves_per_eu(5))) k_matter_source(MatterArgs<S> a) {
   const int64_t gt = (int64_t)blockIdx.x * MBLOCK + threadIdx.x;
   const int64_t z = gt >> a.lg;
   const int g = (int)(gt & ((1 << a.lg) - 1));
@@ -149,75 +291,71 @@ __global__ void __launch_bounds__(MBLOCK) k_matter_source(MatterArgs<S> a) {
   const double Em = on ? (double)a.E[zg] : 0.0;
   const double cv = a.cv[z], k0 = a.kappa0[z], Tm = a.T[z];
   const double kq = on ? k0 * a.tab.kg[gg] : 0.0;
-  const double nuc = a.tab.nu_c[gg], nhi = a.tab.nu_edge[gg + 1];
   const double cdt = a.c * a.dt;
-  const double hs = planck_low(PLANCK_SPLIT), hh = planck_high(PLANCK_SPLIT);
-  const double pnorm = a.tab.a_rad * 15.0 / (M_PI * M_PI * M_PI * M_PI);
+  const GroupLane gr(a.tab, a.G, g, a.lg);
 
-  // the group's opacity and inner update at temperature T; r(T) summed over the zone.  A lane
-  // evaluates the Planck integral at its group's lower edge and takes the upper edge's value
-  // from the next lane (the zone's last lane evaluates its upper edge itself; lanes past the
-  // last group evaluate the top edge)
-  const int lpz = 1 << a.lg;
-  const double nedge = a.tab.nu_edge[g < a.G ? g : a.G];
-  const double ntop = a.tab.nu_edge[a.G];
-  const int up = (((int)threadIdx.x + 1) & 63) << 2;   // byte address of the next lane (a zone's
-                                                          // last lane does not use it)
-  auto inner = [&](double T, double& kap) {
-    const double iT = 1.0 / T;
-    kap = kq * sqrt(iT) * -expm1(-nuc * iT);
-    const double xa = nedge * iT;
-    const double va = planck_edge(xa);
-    const double vn = lane_value(up, va);
-    const double xb = nhi * iT;
-    const double vb = (g == lpz - 1) ? planck_edge(ntop * iT) : vn;
-    const double T2 = T * T;
-    const double B = pnorm * T2 * T2 * planck_part_v(xa, xb, va, vb, hs, hh);
-    return (Em + cdt * kap * B) / (1.0 + cdt * kap);
-  };
+  // r(T) = cv (T - T^-) + sum_g (E_g(T) - E_g^-), E_g(T) - E_g^- = c dt kappa (B - E^-) / (1 + c dt kappa)
   auto residual = [&](double T) {
-    double kap;
-    const double E = inner(T, kap);
-    return cv * (T - Tm) + zone_sum(on ? E - Em : 0.0, a.lg);
+    double kap, B;
+    gr.at<1>(&T, kq, &kap, &B);
+    const double ck = cdt * kap;
+    return cv * (T - Tm) + zone_sum(on ? ck * (B - Em) * rcp2(1.0 + ck) : 0.0, a.lg);
+  };
+  // r(T) and r(T + h), h = 1e-7 T
+  auto residual2 = [&](double T, double& r, double& rh) {
+    const double Tp[2] = {T, T + 1e-7 * T};
+    double kap[2], B[2], s[2];
+    gr.at<2>(Tp, kq, kap, B);
+    for (int p = 0; p < 2; ++p) {
+      const double ck = cdt * kap[p];
+      s[p] = zone_sum(on ? ck * (B[p] - Em) * rcp2(1.0 + ck) : 0.0, a.lg);
+    }
+    r = cv * (Tp[0] - Tm) + s[0];
+    rh = cv * (Tp[1] - Tm) + s[1];
   };
 
-  // outer solve: Newton with a forward-difference derivative and backtracking, then bisection
-  double T = Tm, r = residual(Tm), T1 = Tm;
-  int it_out = 0;
+  // outer solve: Newton with a forward-difference derivative and backtracking, then bisection.
+  // One loop over trial temperatures Tn (one copy of the residual's code): the first is T^-,
+  // taken as it is; a later one replaces T where it lowers |r|, else the step is halved
+  double T = Tm, Tn = Tm, r = 0.0, T1 = Tm, d = 0.0, lam = 1.0;
+  int it = -1, ls = 0, it_out = 0;
   bool done = false;
-  for (int it = 0; it < a.tab.maxn && !done; ++it) {
-    const double h = 1e-7 * T;
-    const double J = (residual(T + h) - r) / h;
-    if (!(J > 0.0)) break;
-    const double d = -r / J;
-    if (fabs(d) <= a.tab.tol * T) {
-      T1 = T + d;
-      it_out = it + 1;
-      done = true;
-      break;
-    }
-    double lam = 1.0, Tn = T, rn = r;
-    bool ok = false;
-    for (int ls = 0; ls <= 10; ++ls) {
-      Tn = T + lam * d;
-      if (Tn > 0.0) {
-        rn = residual(Tn);
-        if (fabs(rn) < fabs(r)) {
-          ok = true;
-          break;
-        }
+  while (true) {
+    double rn, rhn;
+    residual2(Tn, rn, rhn);
+    if (it < 0 || fabs(rn) < fabs(r)) {
+      const bool conv = it >= 0 && fabs(Tn - T) <= a.tab.tol * Tn;
+      T = Tn;
+      r = rn;
+      ++it;
+      if (conv) {
+        T1 = T;
+        it_out = it;
+        done = true;
+        break;
       }
+      if (it >= a.tab.maxn) break;
+      const double h = 1e-7 * T;
+      const double dr = rhn - rn;   // J h
+      if (!(dr > 0.0)) break;
+      d = -r * h * rcp2(dr);
+      if (fabs(d) <= a.tab.tol * T) {
+        T1 = T + d;
+        it_out = it + 1;
+        done = true;
+        break;
+      }
+      lam = 1.0;
+      ls = 0;
+    } else {
       lam *= 0.5;
+      ++ls;
     }
-    if (!ok) break;
-    const bool conv = fabs(Tn - T) <= a.tab.tol * Tn;
-    T = Tn;
-    r = rn;
-    if (conv) {
-      T1 = T;
-      it_out = it + 1;
-      done = true;
+    while (ls <= 10 && !((Tn = T + lam * d) > 0.0)) {
+      lam *= 0.5;
+      ++ls;
     }
+    if (ls > 10) break;
   }
   if (!done) {
     const double esum = zone_sum(on ? fmax(Em, 0.0) : 0.0, a.lg);
@@ -235,13 +373,13 @@ __global__ void __launch_bounds__(MBLOCK) k_matter_source(MatterArgs<S> a) {
     it_out = -steps;
   }
 
-  // the groups at T^{n+1}, the fluxes with the new opacity
+  // the groups at T^{n+1}, the fluxes with the new opacity (every lane of the zone calls)
+  double kap, B;
+  gr.at<1>(&T1, kq, &kap, &B);
   if (on) {
-    double kap;
-    const double E1 = inner(T1, kap);
-    a.E[zg] = (S)E1;
-    const double den = 1.0 + cdt * (kap + (double)a.sig[zg]);
-    for (int k = 0; k < a.ndim; ++k) a.F[k][zg] = (S)((double)a.F[k][zg] / den);
+    a.E[zg] = (S)((Em + cdt * kap * B) * rcp2(1.0 + cdt * kap));
+    const double iden = rcp2(1.0 + cdt * (kap + (double)a.sig[zg]));
+    for (int k = 0; k < a.ndim; ++k) a.F[k][zg] = (S)((double)a.F[k][zg] * iden);
   }
   if (g == 0) {
     a.T[z] = T1;
@@ -280,7 +418,7 @@ template <typename S>
 int launch_matter_coeffs_t(fornax_m1_ctx* ctx, const fornax_m1_matter* m, void* kap, void* B, hipStream_t st) {
   MatterArgs<S> a;
   fill_matter<S>(ctx, a, m);
-  const int64_t n = a.nzones * a.G;
+  const int64_t n = a.nzones << a.lg;
   if (n == 0) return FORNAX_OK;
   hipLaunchKernelGGL(k_matter_coeffs<S>, dim3((unsigned)((n + MBLOCK - 1) / MBLOCK)), dim3(MBLOCK), 0, st, a, (S*)kap,
                      (S*)B);
