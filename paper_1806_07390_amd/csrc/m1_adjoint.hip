@@ -158,8 +158,7 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
   // march face f (between planes f-1 and f) from window planes f-2 .. f+1 (q0 .. q3), the total
   // opacities and mu of planes f-1, f
   auto march_face_r = [&](int f, const R q0[4], const R q1[4], const R q2[4], const R q3[4], R ks1, R ks2,
-                          const R mu1[4], const R mu2[4], R fl[4], R C[4][4], R& dkL, R& dkR) {
-    for (int v = 0; v < 4; ++v) fl[v] = R(0);
+                          const R mu1[4], const R mu2[4], R C[4][4], R& dkL, R& dkR) {
     for (int p = 0; p < 4; ++p)
       for (int v = 0; v < 4; ++v) C[p][v] = R(0);
     dkL = dkR = R(0);
@@ -173,11 +172,11 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
       qq[2][v] = q2[v];
       qq[3][v] = q3[v];
     }
-    face_vjp_cart<R, DIM, LIM>(a, MD < 0 ? 0 : MD, geo.dx[MD < 0 ? 0 : MD], qq, ks1, ks2, nu, fl, C, dkL, dkR);
+    face_vjp_cart<R, DIM, LIM>(a, MD < 0 ? 0 : MD, geo.dx[MD < 0 ? 0 : MD], qq, ks1, ks2, nu, C, dkL, dkR);
   };
   // (the window rows in ring order)
-  auto march_face = [&](int f, R fl[4], R C[4][4], R& dkL, R& dkR) {
-    march_face_r(f, wq[0], wq[1], wq[2], wq[3], wks[1], wks[2], wmu[1], wmu[2], fl, C, dkL, dkR);
+  auto march_face = [&](int f, R C[4][4], R& dkL, R& dkR) {
+    march_face_r(f, wq[0], wq[1], wq[2], wq[3], wks[1], wks[2], wmu[1], wmu[2], C, dkL, dkR);
   };
   if constexpr (DIM >= 2) {
     if (colin) {
@@ -196,8 +195,8 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
           }
           load_plane_w(f + 1, wq[3], wks[3], wmu[3]);
         }
-        R fl[4], C[4][4], dkL, dkR;
-        march_face(f, fl, C, dkL, dkR);
+        R C[4][4], dkL, dkR;
+        march_face(f, C, dkL, dkR);
         // face f contributes to zones f-2+p, i.e. ring slot i-3+p
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -233,9 +232,9 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
     if constexpr (DIM >= 2) {
       if (colin) {
         load_plane_w(m + 3, wq[sl(3)], wks[sl(3)], wmu[sl(3)]);
-        R fl[4], C[4][4], dkL, dkR;
+        R C[4][4], dkL, dkR;
         march_face_r(m + 2, wq[sl(0)], wq[sl(1)], wq[sl(2)], wq[sl(3)], wks[sl(1)], wks[sl(2)], wmu[sl(1)],
-                     wmu[sl(2)], fl, C, dkL, dkR);
+                     wmu[sl(2)], C, dkL, dkR);
         for (int p = 0; p < 4; ++p)
           for (int v = 0; v < NC; ++v) racc[sl(p)][v] += C[p][v];
         rdk[sl(1)] += dkL;
@@ -275,7 +274,7 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
     // ---- x face x0 - 1 + cx ----
     {
       const int f = x0 - 1 + cx;
-      R fl[4] = {R(0), R(0), R(0), R(0)}, C[4][4], dkL = R(0), dkR = R(0);
+      R C[4][4], dkL = R(0), dkR = R(0);
       for (int p = 0; p < 4; ++p)
         for (int v = 0; v < 4; ++v) C[p][v] = R(0);
       if (rowin && (wx || (f >= 0 && f <= n0))) {
@@ -286,7 +285,7 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
         }
         R nu[4] = {R(0), R(0), R(0), R(0)};
         for (int v = 0; v < NC; ++v) nu[v] = nux * (pv(NC + 1 + v, cx + 2) - pv(NC + 1 + v, cx + 1));
-        face_vjp_cart<R, DIM, LIM>(a, 0, dx0, q, pv(NC, cx + 1), pv(NC, cx + 2), nu, fl, C, dkL, dkR);
+        face_vjp_cart<R, DIM, LIM>(a, 0, dx0, q, pv(NC, cx + 1), pv(NC, cx + 2), nu, C, dkL, dkR);
       }
       for (int p = 0; p < 4; ++p)
         for (int v = 0; v < NC; ++v) cxr(p, v, cx) = C[p][v];
@@ -530,7 +529,7 @@ static int launch_adjoint_t(fornax_m1_ctx* ctx, const Geo<R>& geo, const fornax_
   a.nzones = (int64_t)D.n[0] * D.n[1] * D.n[2];
   a.c = D.c;
   a.dt = dt;
-  a.f2_fp64 = D.f_fp64 * D.f_fp64;
+  fill_closure_constants(a, D);
   a.inflow = inflow;
   a.E = (const S*)Un->E;
   a.Eo = nullptr;

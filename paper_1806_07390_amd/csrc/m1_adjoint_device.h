@@ -157,13 +157,13 @@ __device__ __forceinline__ void closure_row_vjp(const R q[4], int d, R c, int ed
   }
 }
 
-// Forward flux and VJP of one face (uniform Cartesian): stencil zones q[0..3] = f-2 .. f+1,
-// total opacities of zones f-1, f, face adjoint nu (the adjoint of the face flux).  Outputs
-// the forward flux, the contributions C[p] to the adjoints of the four stencil zones and the
-// adjoint contributions to kappa of zones f-1 (dkL) and f (dkR) through epsilon.
+// VJP of the flux of one face (uniform Cartesian): stencil zones q[0..3] = f-2 .. f+1, total
+// opacities of zones f-1, f, face adjoint nu (the adjoint of the face flux).  Outputs the
+// contributions C[p] to the adjoints of the four stencil zones and the adjoint contributions
+// to kappa of zones f-1 (dkL) and f (dkR) through epsilon.
 template <typename R, int ND, int LIM = -1>
 __device__ __forceinline__ void face_vjp_cart(const StepArgsBase& a, int d, R dx, const R q[4][4], R ksL, R ksR,
-                                              const R nu[4], R flux[4], R C[4][4], R& dkL, R& dkR) {
+                                              const R nu[4], R C[4][4], R& dkL, R& dkR) {
   const R c = R(a.c);
   ReconRec<R, ND> rl, rr;
   reconstruct_rec<R, ND, LIM>(a, q[0], q[1], q[2], true, true, rl);
@@ -175,9 +175,6 @@ __device__ __forceinline__ void face_vjp_cart(const StepArgsBase& a, int d, R dx
   const bool thick = tau > R(1);
   const R itau = thick ? rcp_(tau) : R(1);
   const R eps = itau;
-  // forward flux
-  const R one[3] = {R(1), R(1), R(1)};
-  hll<R, false, ND>(a, d, qL, qR, one, one, eps, flux);
   // adjoint of the HLL flux
   R gL[4] = {R(0), R(0), R(0), R(0)}, gR[4] = {R(0), R(0), R(0), R(0)};
   const R half = R(0.5);

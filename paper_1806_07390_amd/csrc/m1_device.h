@@ -173,6 +173,22 @@ __device__ __forceinline__ void fetch(const StepArgs<S>& a, const Geo<R>& geo, i
   for (int c = ND; c < 3; ++c) q[1 + c] = R(0);
 }
 
+// |F^|^2 (F^_k = F_k / h_k, ih = 1/h) and cE of a face state, as the realizability check forms
+// them; the closure in double starts from the same two values.
+template <typename R>
+struct FaceAux {
+  R F2, X;
+};
+template <typename R, bool SPH, int ND>
+__device__ __forceinline__ FaceAux<R> face_aux(const R q[4], const R ih[3], R c) {
+  FaceAux<R> x{R(0), c * q[0]};
+  for (int k = 0; k < ND; ++k) {
+    const R fk = SPH ? q[1 + k] * ih[k] : q[1 + k];
+    x.F2 += fk * fk;
+  }
+  return x;
+}
+
 // E > 0 and |F^| <= cE with F^_k = F_k / h_k (ih = 1/h)
 template <typename R, bool SPH, int ND>
 __device__ __forceinline__ bool realizable(const R q[4], const R ih[3], R c) {
@@ -190,11 +206,12 @@ __device__ __forceinline__ bool realizable(const R q[4], const R ih[3], R c) {
 // either is not realizable.
 // LIM: the limiter when known at compile time (a FORNAX_LIMITER_* value), -1 to read it from
 // the arguments.  vs (spherical grids, nullable): the zone's idm, idp, dlo, dhi, idc of the
-// tables, when the caller already holds them.
+// tables, when the caller already holds them.  alo, ahi (nullable): the face states' |F^|^2 and cE.
 template <typename R, bool SPH, int ND, int LIM = -1>
 __device__ __forceinline__ void reconstruct(const StepArgsBase& a, const Geo<R>& geo, int d, int e, const R qm[4],
                                             const R q0[4], const R qp[4], const R ihlo[3], const R ihhi[3],
-                                            bool lo_open, bool hi_open, R lo[4], R hi[4], const R* vs = nullptr) {
+                                            bool lo_open, bool hi_open, R lo[4], R hi[4], const R* vs = nullptr,
+                                            FaceAux<R>* alo = nullptr, FaceAux<R>* ahi = nullptr) {
   const R c = R(a.c);
   const int limiter = (LIM >= 0) ? LIM : a.limiter;
   R s[4];
@@ -292,15 +309,20 @@ __device__ __forceinline__ void reconstruct(const StepArgsBase& a, const Geo<R>&
       hi[cp] = q0[cp] + s[cp] * dh;
     }
   }
-  const bool ok =
-      (!lo_open || realizable<R, SPH, ND>(lo, ihlo, c)) && (!hi_open || realizable<R, SPH, ND>(hi, ihhi, c));
+  FaceAux<R> xl = face_aux<R, SPH, ND>(lo, ihlo, c), xh = face_aux<R, SPH, ND>(hi, ihhi, c);
+  const bool ok = (!lo_open || (lo[0] > R(0) && xl.F2 <= xl.X * xl.X)) &&
+                  (!hi_open || (hi[0] > R(0) && xh.F2 <= xh.X * xh.X));
   // the fallback is rare: the selects only run in a wave where some lane needs it
   if (__builtin_amdgcn_ballot_w64(!ok)) {
     for (int cp = 0; cp <= ND; ++cp) {
       lo[cp] = ok ? lo[cp] : q0[cp];
       hi[cp] = ok ? hi[cp] : q0[cp];
     }
+    if (alo) xl = face_aux<R, SPH, ND>(lo, ihlo, c);
+    if (ahi) xh = face_aux<R, SPH, ND>(hi, ihhi, c);
   }
+  if (alo) *alo = xl;
+  if (ahi) *ahi = xh;
   for (int cp = ND + 1; cp < 4; ++cp) lo[cp] = hi[cp] = R(0);
 }
 
@@ -339,65 +361,75 @@ __device__ __forceinline__ void closure_full(const R q[4], const R ih[3], R c, i
   P[8] += iso;
 }
 
-// Row d of the closure, P^^{dk} for k < ND.  In double, from E and F directly (one square
-// root, one reciprocal); in the MIXED path (R = float) from f = F/(cE), in double where
-// f^2 >= f2_fp64.
-template <typename R, bool SPH, int ND>
-__device__ __forceinline__ void closure_row(const R q[4], const R ih[3], int d, R c, int eddington, double f2_fp64,
-                                            R P[3]) {
-  const R E = q[0];
-  for (int k = 0; k < 3; ++k) P[k] = R(0);
-  if (eddington || !(E > R(0))) {
-    P[d] = E * R(1.0 / 3.0);
+// c times row d of the closure, T_k = c P^^{dk} for k < ND, in double: with X = cE and
+// S = sqrt(X^2 - 3/4 |F|^2) (half of cE s),
+//   T = (2 S - X)/3 delta + (3/2) F F / (X + S),
+// one square root and one reciprocal, nothing cancelling more than an ulp of E, and no constant
+// but c itself.  x: |F^|^2 and cE of the state, as its realizability check formed them.
+// (The 512^2 x 16 blob steps take 1 to 2 % less than with P from (S - cE)/(3c) and
+// 3 F F/(c (2 cE + S)) and the check's values formed again.)
+template <bool SPH, int ND>
+__device__ __forceinline__ void closure_row_d(const StepArgsBase& a, const double q[4], const double ih[3],
+                                              const FaceAux<double>& x, int d, double T[3]) {
+  if (a.closure) {
+    for (int k = 0; k < ND; ++k) T[k] = k == d ? x.X * (1.0 / 3.0) : 0.0;
     return;
   }
-  if constexpr (sizeof(R) == 8) {
-    // double: from E and F directly, with S = cE s = sqrt(4 (cE)^2 - 3 |F|^2),
-    //   P = (S - cE)/(3c) delta + 3 F F / (c (2 cE + S)),
-    // one square root and one reciprocal.  The tensor is homogeneous of degree one in
-    // (E, F): a state with cE below 2^-450, whose squares could underflow, is evaluated
-    // scaled by 2^600 (exact) and the row scaled back (only in waves that hold one).
-    R Fh[3] = {R(0), R(0), R(0)};
-    for (int k = 0; k < ND; ++k) Fh[k] = SPH ? q[1 + k] * ih[k] : q[1 + k];
-    const R cE = c * E;
-    R F2 = R(0);
-    for (int k = 0; k < ND; ++k) F2 += Fh[k] * Fh[k];
-    const R A = cE * cE;
-    {
-      const R S = sqrt_(R(4) * A - R(3) * F2);
-      const R iso = (S - cE) * rcp_(R(3) * c);   // c is uniform: hoisted
-      const R af = R(3) * rcp_(c * (R(2) * cE + S)) * Fh[d];
-      for (int k = 0; k < ND; ++k) P[k] = af * Fh[k] + (k == d ? iso : R(0));
-    }
-    // the rare states are evaluated again, in a branch taken only by waves that hold one (the
-    // empty asm keeps the compiler from computing it in every wave): |f| > 1 with the direction
-    // of F at |f| = 1, and states with cE below 2^-450, whose squares could underflow, scaled
-    // by 2^600 (exact) and the row scaled back
-    const bool rare = cE < R(0x1p-450) || F2 > A;
-    if (__builtin_amdgcn_ballot_w64(rare)) {
-      __asm__ volatile("");
-      if (rare) {
-        const bool scl = cE < R(0x1p-450);
-        const R sc0 = scl ? R(0x1p600) : R(1);
-        const R cEs = cE * sc0;
-        R F2s = R(0);
+  double Fh[3] = {0.0, 0.0, 0.0};
+  for (int k = 0; k < ND; ++k) Fh[k] = SPH ? q[1 + k] * ih[k] : q[1 + k];
+  const double A = x.X * x.X;
+  {
+    const double S = sqrt_(fma(-0.75, x.F2, A));
+    const double w = 1.5 * rcp_(x.X + S) * Fh[d];
+    const double iso = fma(2.0, S, -x.X) * (1.0 / 3.0);
+    for (int k = 0; k < ND; ++k) T[k] = k == d ? fma(w, Fh[k], iso) : w * Fh[k];
+  }
+  // the rare states are evaluated again, in a branch taken only by waves that hold one (the
+  // empty asm keeps the compiler from computing it in every wave): the Eddington value for
+  // E <= 0, |f| > 1 with the direction of F at |f| = 1, and states with cE below 2^-450, whose
+  // squares could underflow, scaled by 2^600 (exact; the tensor is homogeneous of degree one in
+  // (E, F)) and the row scaled back
+  const bool rare = !(x.X >= 0x1p-450) || x.F2 > A;
+  if (__builtin_amdgcn_ballot_w64(rare)) {
+    __asm__ volatile("");
+    if (rare) {
+      if (!(x.X > 0.0)) {
+        for (int k = 0; k < ND; ++k) T[k] = k == d ? x.X * (1.0 / 3.0) : 0.0;
+      } else {
+        const bool scl = x.X < 0x1p-450;
+        const double sc0 = scl ? 0x1p600 : 1.0;
+        const double Xs = x.X * sc0;
+        double F2 = 0.0;
         for (int k = 0; k < ND; ++k) {
           Fh[k] *= sc0;
-          F2s += Fh[k] * Fh[k];
+          F2 += Fh[k] * Fh[k];
         }
-        const R As = cEs * cEs;
-        if (F2s > As) {
-          const R sc = cEs * rcp_(sqrt_(F2s));
+        const double As = Xs * Xs;
+        if (F2 > As) {
+          const double sc = Xs * rcp_(sqrt_(F2));
           for (int k = 0; k < ND; ++k) Fh[k] *= sc;
-          F2s = As;
+          F2 = As;
         }
-        const R S = sqrt_(R(4) * As - R(3) * F2s);
-        const R iso = (S - cEs) * rcp_(R(3) * c);
-        const R af = R(3) * rcp_(c * (R(2) * cEs + S)) * Fh[d];
-        const R sb = scl ? R(0x1p-600) : R(1);
-        for (int k = 0; k < ND; ++k) P[k] = (af * Fh[k] + (k == d ? iso : R(0))) * sb;
+        const double S = sqrt_(fma(-0.75, F2, As));
+        const double w = 1.5 * rcp_(Xs + S) * Fh[d];
+        const double iso = fma(2.0, S, -Xs) * (1.0 / 3.0);
+        const double sb = scl ? 0x1p-600 : 1.0;
+        for (int k = 0; k < ND; ++k) T[k] = (w * Fh[k] + (k == d ? iso : 0.0)) * sb;
       }
     }
+  }
+}
+
+// Row d of the closure, P^^{dk} for k < ND, in the MIXED path (R = float) from f = F/(cE), in
+// double where f^2 >= f2_fp64 (one square root and one reciprocal, as in closure_row_d: the
+// 512^2 x 16 blob step 87 -> 80 us against the form with f, (1 - f^2)/(1 + s) and 3/(2 + s)).
+template <typename R, bool SPH, int ND>
+__device__ __forceinline__ void closure_row(const StepArgsBase& a, const R q[4], const R ih[3], int d, R P[3]) {
+  const R c = R(a.c);
+  const R E = q[0];
+  for (int k = 0; k < 3; ++k) P[k] = R(0);
+  if (a.closure || !(E > R(0))) {
+    P[d] = E * R(1.0 / 3.0);
     return;
   }
   R f[3] = {R(0), R(0), R(0)};
@@ -407,25 +439,29 @@ __device__ __forceinline__ void closure_row(const R q[4], const R ih[3], int d, 
     f[k] = (SPH ? q[1 + k] * ih[k] : q[1 + k]) * icE;
     f2 += f[k] * f[k];
   }
-  if constexpr (sizeof(R) == 4) {
-    if ((double)f2 >= f2_fp64) {
-      double fd[3] = {0.0, 0.0, 0.0}, f2d = 0.0;
-      const double icEd = rcp_((double)c * (double)E);
+  {
+    if (f2 >= a.f2_fp64) {
+      // P = (S - cE)/(3c) delta + 3 F F/(c (2cE + S)) with |F| clamped to cE (the squares of
+      // floats neither overflow nor underflow in double)
+      double Fh[3] = {0.0, 0.0, 0.0}, F2 = 0.0;
+      const double cE = a.cd * (double)E;
       for (int k = 0; k < ND; ++k) {
-        fd[k] = (SPH ? (double)q[1 + k] * (double)ih[k] : (double)q[1 + k]) * icEd;
-        f2d += fd[k] * fd[k];
+        Fh[k] = SPH ? (double)q[1 + k] * (double)ih[k] : (double)q[1 + k];
+        F2 += Fh[k] * Fh[k];
       }
-      if (f2d > 1.0) {
-        const double sc = rcp_(sqrt_(f2d));
-        for (int k = 0; k < ND; ++k) fd[k] *= sc;
-        f2d = 1.0;
+      const double A = cE * cE;
+      double S = sqrt_(4.0 * A - 3.0 * F2), sc2 = 1.0;
+      if (__builtin_amdgcn_ballot_w64(F2 > A)) {
+        __asm__ volatile("");
+        // |f| > 1: F F scaled by (cE/|F|)^2, S = cE
+        if (F2 > A) {
+          sc2 = A * rcp_(F2);
+          S = cE;
+        }
       }
-      // the cancellation-free form (1 - f^2)/(1 + s) in double near free streaming
-      const double s = sqrt_(4.0 - 3.0 * f2d);
-      const double r = rcp_((1.0 + s) * (2.0 + s));
-      const double iso = (double)E * (1.0 - f2d) * (2.0 + s) * r;
-      const double ani = (double)E * 3.0 * (1.0 + s) * r;
-      for (int k = 0; k < ND; ++k) P[k] = (R)(ani * fd[d] * fd[k] + (k == d ? iso : 0.0));
+      const double iso = (S - cE) * a.i3c;
+      const double af = 3.0 * rcp_(a.cd * (2.0 * cE + S)) * Fh[d] * sc2;
+      for (int k = 0; k < ND; ++k) P[k] = (R)(af * Fh[k] + (k == d ? iso : 0.0));
       return;
     }
   }
@@ -475,13 +511,25 @@ __device__ __forceinline__ void m1_speeds(R E, R Fn, R c, int closure, R& lo, R&
 // inverses ih, left/right states qL, qR and the correction factor eps of the energy flux.
 // S_R = -S_L = c; with WS, a launch whose wavespeed option asks for them takes the HLLE bounds
 // from the M1 characteristic speeds of both states instead.
+// xL, xR (double only, nullable): the states' |F^|^2 and cE with this face's scale factors.
 template <typename R, bool SPH, int ND, bool WS = false>
 __device__ __forceinline__ void hll(const StepArgsBase& a, int d, const R qL[4], const R qR[4], const R h[3],
-                                    const R ih[3], R eps, R flux[4]) {
+                                    const R ih[3], R eps, R flux[4], const FaceAux<R>* xL = nullptr,
+                                    const FaceAux<R>* xR = nullptr) {
   const R c = R(a.c);
-  R PL[3], PR[3];
-  closure_row<R, SPH, ND>(qL, ih, d, c, a.closure, a.f2_fp64, PL);
-  closure_row<R, SPH, ND>(qR, ih, d, c, a.closure, a.f2_fp64, PR);
+  R PL[3], PR[3];      // double: c P
+  FaceAux<R> aL{}, aR{};
+  if constexpr (sizeof(R) == 8) {
+    aL = xL ? *xL : face_aux<R, SPH, ND>(qL, ih, c);
+    aR = xR ? *xR : face_aux<R, SPH, ND>(qR, ih, c);
+    closure_row_d<SPH, ND>(a, qL, ih, aL, d, PL);
+    closure_row_d<SPH, ND>(a, qR, ih, aR, d, PR);
+  } else {
+    closure_row<R, SPH, ND>(a, qL, ih, d, PL);
+    closure_row<R, SPH, ND>(a, qR, ih, d, PR);
+  }
+  // c^2 P^d_k from the row: c times it in double (the row is c P there)
+  const R cc = sizeof(R) == 8 ? c : c * c;
   R ihd = R(1), S = c;
   if constexpr (SPH) {
     ihd = ih[d];
@@ -497,19 +545,33 @@ __device__ __forceinline__ void hll(const StepArgsBase& a, int d, const R qL[4],
       flux[0] = (SR * (qL[1 + d] * (ihd * ihd)) - SL * (qR[1 + d] * (ihd * ihd)) + eps * SLR * (qR[0] - qL[0])) * id;
       for (int k = 0; k < ND; ++k) {
         const R hk = SPH ? h[k] * ihd : R(1);
-        flux[1 + k] = (SR * (c * c * PL[k] * hk) - SL * (c * c * PR[k] * hk) + SLR * (qR[1 + k] - qL[1 + k])) * id;
+        flux[1 + k] = (SR * (cc * PL[k] * hk) - SL * (cc * PR[k] * hk) + SLR * (qR[1 + k] - qL[1 + k])) * id;
       }
       for (int k = ND; k < 3; ++k) flux[1 + k] = R(0);
       return;
     }
   }
   const R half = R(0.5);
-  // energy: F^d = F_d / h_d^2; S_R = -S_L = S
-  flux[0] = half * ((qL[1 + d] + qR[1 + d]) * (ihd * ihd)) - half * eps * S * (qR[0] - qL[0]);
-  // covariant flux components: c^2 P^d_k = c^2 P^^{dk} h_k / h_d
-  for (int k = 0; k < ND; ++k) {
-    const R hk = SPH ? h[k] * ihd : R(1);
-    flux[1 + k] = half * c * c * (PL[k] + PR[k]) * hk - half * S * (qR[1 + k] - qL[1 + k]);
+  if constexpr (sizeof(R) == 8) {
+    // energy: F^d = F_d / h_d^2, S_R = -S_L = c / h_d (S (E_R - E_L) = (X_R - X_L) / h_d);
+    // covariant flux components: c^2 P^d_k = c T^{dk} h_k / h_d
+    const R hc = half * c;
+    if constexpr (SPH) {
+      flux[0] = half * ihd * ((qL[1 + d] + qR[1 + d]) * ihd - eps * (aR.X - aL.X));
+      for (int k = 0; k < ND; ++k)
+        flux[1 + k] = hc * ihd * ((PL[k] + PR[k]) * h[k] - (qR[1 + k] - qL[1 + k]));
+    } else {
+      flux[0] = half * ((qL[1 + d] + qR[1 + d]) - eps * (aR.X - aL.X));
+      for (int k = 0; k < ND; ++k) flux[1 + k] = hc * ((PL[k] + PR[k]) - (qR[1 + k] - qL[1 + k]));
+    }
+  } else {
+    // energy: F^d = F_d / h_d^2; S_R = -S_L = S
+    flux[0] = half * ((qL[1 + d] + qR[1 + d]) * (ihd * ihd)) - half * eps * S * (qR[0] - qL[0]);
+    // covariant flux components: c^2 P^d_k = c^2 P^^{dk} h_k / h_d
+    for (int k = 0; k < ND; ++k) {
+      const R hk = SPH ? h[k] * ihd : R(1);
+      flux[1 + k] = half * c * c * (PL[k] + PR[k]) * hk - half * S * (qR[1 + k] - qL[1 + k]);
+    }
   }
   for (int k = ND; k < 3; ++k) flux[1 + k] = R(0);
 }
@@ -518,6 +580,16 @@ template <typename R>
 __device__ __forceinline__ R epsilon_of(R ksL, R ksR, R dlL, R dlR) {
   const R tau = R(0.5) * (ksL + ksR) * (R(0.5) * (dlL + dlR));
   // the reciprocal only in a wave where some face is optically thick
+  R eps = R(1);
+  if (__builtin_amdgcn_ballot_w64(tau > R(1))) eps = (tau > R(1)) ? rcp_(tau) : R(1);
+  return eps;
+}
+
+// The same on uniform Cartesian zones, hdx = dx/2: halving is exact, so the value is the same with
+// two operations less.
+template <typename R>
+__device__ __forceinline__ R epsilon_uniform(R ksL, R ksR, R hdx) {
+  const R tau = (ksL + ksR) * hdx;
   R eps = R(1);
   if (__builtin_amdgcn_ballot_w64(tau > R(1))) eps = (tau > R(1)) ? rcp_(tau) : R(1);
   return eps;
@@ -579,25 +651,30 @@ struct ZoneDiag {
 // The coefficients enter as cdtk = c dt kappa, cdtks = c dt (kappa + sigma) and the emission
 // term jB = c dt kappa B, all in double.  Returns E^{n+1} - E^- and the new state in the
 // storage type (E1, F1); the caller stores it.  (i, j) are the zone's x and y indices.
-template <typename S, typename R, bool SPH, int ND>
-__device__ __forceinline__ double source_zone(const StepArgsBase& a, const Geo<R>& geo, int i, int j, const R Um[4],
-                                              double cdtk, double cdtks, double jB, bool want_diag, double V,
-                                              ZoneDiag& zd, S& E1o, S F1o[3]) {
-  const double c = a.c;
+// source_update: the update alone.
+template <typename S, typename R, int ND>
+__device__ __forceinline__ double source_update(const R Um[4], double cdtk, double cdtks, double jB, S& E1o,
+                                                S F1o[3]) {
   const double Emd = (double)Um[0];
   // one reciprocal for both denominators: 1/(1+x) = (1+y) / ((1+x)(1+y))
   const double dE = 1.0 + cdtk, dF = 1.0 + cdtks;
   const double rr = rcp_(dE * dF);
   const double E1 = (Emd + jB) * (dF * rr);
   const double ifden = dE * rr;
-  const S E1s = (S)E1;
-  E1o = E1s;
+  E1o = (S)E1;
+  for (int cc = 0; cc < ND; ++cc) F1o[cc] = (S)((double)Um[1 + cc] * ifden);
+  return (double)E1o - Emd;
+}
+
+template <typename S, typename R, bool SPH, int ND>
+__device__ __forceinline__ double source_zone(const StepArgsBase& a, const Geo<R>& geo, int i, int j, const R Um[4],
+                                              double cdtk, double cdtks, double jB, bool want_diag, double V,
+                                              ZoneDiag& zd, S& E1o, S F1o[3]) {
+  const double c = a.c;
+  const double dz = source_update<S, R, ND>(Um, cdtk, cdtks, jB, E1o, F1o);
+  const S E1s = E1o;
   double F1s[3] = {0.0, 0.0, 0.0};
-  for (int cc = 0; cc < ND; ++cc) {
-    const S v = (S)((double)Um[1 + cc] * ifden);
-    F1o[cc] = v;
-    F1s[cc] = (double)v;
-  }
+  for (int cc = 0; cc < ND; ++cc) F1s[cc] = (double)F1o[cc];
   const double E1d = (double)E1s;
   if (want_diag) {
     zd.energy += V * E1d;
@@ -630,7 +707,7 @@ __device__ __forceinline__ double source_zone(const StepArgsBase& a, const Geo<R
     zd.nun += (lim < 0.0 || F2 > lim * lim) ? 1 : 0;
     zd.nnp += (E1d > 0.0) ? 0 : 1;
   }
-  return E1d - Emd;
+  return dz;
 }
 
 }  // namespace fm1

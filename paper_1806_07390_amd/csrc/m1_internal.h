@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
 #include <vector>
 
 #include "fornax_m1.h"
@@ -76,9 +77,21 @@ struct StepArgsBase {
   int zones_per_block;
   int64_t nzones;
   double c, dt;
-  double f2_fp64;            // (f_fp64)^2, MIXED only
+  float f2_fp64;             // the smallest float at or above f_fp64^2 (MIXED only)
+  double cd, i3c;            // c as the kernel's type holds it, 1 / (3 cd)
   const double* inflow;      // [G][1+ndim] or null
 };
+
+// The constants of the closure: c as the context's type holds it and its third's reciprocal
+// (kernel arguments, so that they cost no vector registers), and the smallest float at or above
+// f_fp64^2 (f^2 >= it in float decides as f^2 >= f_fp64^2 in double).
+inline void fill_closure_constants(StepArgsBase& a, const fornax_m1_desc& D) {
+  a.cd = D.precision == FORNAX_FP64 ? D.c : (double)(float)D.c;
+  a.i3c = 1.0 / (3.0 * a.cd);
+  const double f2 = D.f_fp64 * D.f_fp64;
+  const float t = (float)f2;
+  a.f2_fp64 = (double)t < f2 ? std::nextafterf(t, INFINITY) : t;
+}
 
 // Ghost rules (periodic wrap, outflow / inflow edge copy, reflect / axis mirror) of the two
 // ghost layers on both sides of every axis.

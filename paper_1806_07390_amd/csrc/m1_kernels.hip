@@ -179,7 +179,7 @@ void fill_args(const fornax_m1_ctx* ctx, StepArgs<S>& a, const fornax_m1_coeffs*
   a.nzones = (int64_t)D.n[0] * D.n[1] * D.n[2];
   a.c = D.c;
   a.dt = dt;
-  a.f2_fp64 = D.f_fp64 * D.f_fp64;
+  fill_closure_constants(a, D);
   a.inflow = inflow;
   a.kap = (const S*)cf->kappa;
   a.sig = (const S*)cf->sigma;

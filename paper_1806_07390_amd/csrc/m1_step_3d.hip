@@ -28,6 +28,14 @@
 //     tiles.
 // One block barrier per plane (after the states), which waits for LDS only: the loads of the
 // next plane stay in flight.  The update of a plane follows the next plane's barrier.
+// What the plane loop waits for is kept out of it by hand: values loaded a plane ahead are moved
+// into registers of their own where they are consumed, so that no copy of a load in flight
+// (with a wait for it) falls before the barrier, every outer-row item is loaded without a branch,
+// and addresses are a uniform base plus a 32-bit lane offset.  192^3 x 12 FP64 3626 -> 3505 us,
+// MIXED 2332 -> 2236 us, 256 x 64 x 128 x 20 MIXED (f mostly above 0.9) 2400 -> 2205 us with the
+// closure's new double form.  Stamps taken inside the loop show where the rest goes in double:
+// of the two waves on a SIMD the older takes a plane in 6800 cycles and waits 3900 at the barrier
+// for the younger one; VALU issue 62 %.
 // With VEL (Cartesian grids), Step 1 of the velocity step: the same transport without the
 // interaction update, each face flux with the advective flux v^d U of the upwind face state
 // added (the face's left state where v^d >= 0), from the normal velocity component on the face;
@@ -48,93 +56,27 @@
 
 #include "m1_device.h"
 #include "m1_internal.h"
+#include "m1_lane.h"
 #include "m1_step.h"
 
 namespace fm1 {
 
-constexpr int C3_TX = 16;   // x columns of a wave row (14 updated)
-
-// the value of the lane one column lower (row_shr:1) / higher (row_shl:1) in the same 16-lane
-// row; the lanes at the row's ends receive 0 (bound_ctrl: they never use it, and no register
-// has to be cleared first)
+// the sign rules: F_c flipped by its sign mask
 template <typename R>
-__device__ __forceinline__ R col_prev(R v) {
-  return __builtin_amdgcn_update_dpp(R(0), v, 0x111, 0xf, 0xf, true);
-}
-template <typename R>
-__device__ __forceinline__ R col_next(R v) {
-  return __builtin_amdgcn_update_dpp(R(0), v, 0x101, 0xf, 0xf, true);
-}
-
-// v of this lane plus v of the lane 16 (S = 16) or 32 (S = 32) apart, by the row swaps of
-// gfx950 (VALU; the lane sums are formed in the same order as a shuffle sum would)
-template <int S>
-__device__ __forceinline__ double lane_pair_sum(double v) {
-  struct W {
-    unsigned lo, hi;
-  };
-  const W w = __builtin_bit_cast(W, v);
-  W a, b;
-  if constexpr (S == 16) {
-    const auto l = __builtin_amdgcn_permlane16_swap(w.lo, w.lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(w.hi, w.hi, false, false);
-    a = W{l[0], h[0]};
-    b = W{l[1], h[1]};
-  } else {
-    const auto l = __builtin_amdgcn_permlane32_swap(w.lo, w.lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(w.hi, w.hi, false, false);
-    a = W{l[0], h[0]};
-    b = W{l[1], h[1]};
-  }
-  return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
-}
-
-// the advective flux v U of the upwind face state added to a face flux (the left state where
-// v >= 0)
-template <typename R>
-__device__ __forceinline__ void add_upwind(R v, const R qL[4], const R qR[4], R flux[4]) {
-  const bool left = v >= R(0);
-  for (int c = 0; c < 4; ++c) flux[c] += v * (left ? qL[c] : qR[c]);
-}
-
-// The ghost rules of one axis, taken from the launch's table at each use (measured: faster
-// than copies of the table held in scalar registers for the whole kernel, which crowd out the
-// other uniform values).
-struct C3Axis {
-  const StepArgsBase* a;
-  int d;
-};
-template <int D>
-__device__ __forceinline__ C3Axis c3_axis(const StepArgsBase& a) { return C3Axis{&a, D}; }
-// Ghost rule of index e (clamped into -2 .. n + 1 first): source zone and flags (bit 0 flips
-// the flux component along the axis), selected without indexing the table by a per-lane value.
-__device__ __forceinline__ void c3_src(const C3Axis& ax, int e, int& src, int& fl) {
-  const StepArgsBase& a = *ax.a;
-  const int D = ax.d;
-  const int n = a.n[D];
-  e = e < -2 ? -2 : (e > n + 1 ? n + 1 : e);
-  src = e;
-  fl = 0;
-  if (e < 0 || e >= n) {
-    const int k = e < 0 ? e + 2 : e - n + 2;
-    src = k == 0 ? a.gsrc[D][0] : k == 1 ? a.gsrc[D][1] : k == 2 ? a.gsrc[D][2] : a.gsrc[D][3];
-    fl = k == 0 ? a.gfl[D][0] : k == 1 ? a.gfl[D][1] : k == 2 ? a.gfl[D][2] : a.gfl[D][3];
-  }
-}
-
-// the sign rules: F_c flipped where bit c - 1 of the mask is set
-template <typename R>
-__device__ __forceinline__ void c3_fix(const R raw[4], int mask, R q[4]) {
+__device__ __forceinline__ void c3_fix(const R raw[4], unsigned mx, unsigned my, unsigned mz, R q[4]) {
   q[0] = raw[0];
-  for (int c = 1; c < 4; ++c) q[c] = ((mask >> (c - 1)) & 1) ? -raw[c] : raw[c];
+  q[1] = flip_sign(raw[1], mx);
+  q[2] = flip_sign(raw[2], my);
+  q[3] = flip_sign(raw[3], mz);
 }
 
+// the state at element offset p of a plane (uniform) plus the lane's byte offset
 template <typename S, typename R>
-__device__ __forceinline__ void c3_load(const StepArgs<S>& a, int off, R q[4]) {
-  q[0] = R(a.E[off]);
-  q[1] = R(a.F[0][off]);
-  q[2] = R(a.F[1][off]);
-  q[3] = R(a.F[2][off]);
+__device__ __forceinline__ void c3_load(const StepArgs<S>& a, int64_t p, unsigned off, R q[4]) {
+  q[0] = R(ld_off(a.E + p, off));
+  q[1] = R(ld_off(a.F[0] + p, off));
+  q[2] = R(ld_off(a.F[1] + p, off));
+  q[3] = R(ld_off(a.F[2] + p, off));
 }
 
 // LDS barrier: waits for the wave's LDS operations only (the global loads of the next plane
@@ -156,8 +98,9 @@ __device__ __forceinline__ void c3_barrier() {
 template <bool AR>
 constexpr int c3_nitem() { return AR ? 20 : 14; }
 
-// NI waves per block, W waves per SIMD (register budget 512 / W)
-template <typename S, int NI, int W, int LIM, bool SPH, bool AR, bool VEL = false>
+// NI waves per block, W waves per SIMD (register budget 512 / W).  RK: whether the launch may be a
+// second Runge-Kutta stage (a.Ea read at run time)
+template <typename S, int NI, int W, int LIM, bool SPH, bool AR, bool VEL = false, bool RK = true>
 __global__ void __launch_bounds__(64 * NI) __attribute__((amdgpu_waves_per_eu(W)))
 k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   using R = S;
@@ -205,13 +148,15 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   c3_src(ax1, yz, ys, yf);
   const bool xedge = x == 0 || x == TX - 1;
   int xef;
-  const int cb = (ys * n0 + xs) * G + g;
+  // byte offsets within a plane (below 2^32: a grid has fewer than 2^29 zone-groups)
+  unsigned ob = (unsigned)((ys * n0 + xs) * G + g) * sizeof(S);
   int xeo;
   c3_src(ax0, x == 0 ? xz - 1 : xz + 1, xeo, xef);
-  const int ceb = (ys * n0 + xeo) * G + g;
-  // flip masks: bit c - 1 flips F_c; a polar-axis ghost row (flag bit 2) also flips F_phi
-  const int lm = (xf & 1) | ((yf & 1) << 1) | (((yf >> 2) & 1) << 2);
-  const int lme = (xef & 1) | ((yf & 1) << 1) | (((yf >> 2) & 1) << 2);
+  unsigned oe = (unsigned)((ys * n0 + xeo) * G + g) * sizeof(S);
+  // sign masks: F_x flips in reflected columns, F_y in reflected or polar-axis rows, F_z in
+  // polar-axis rows (flag bit 2) and in reflected planes
+  const unsigned sx = (unsigned)(xf & 1) << 31, sxe = (unsigned)(xef & 1) << 31;
+  const unsigned sy = (unsigned)(yf & 1) << 31, sz = (unsigned)((yf >> 2) & 1) << 31;
   // spherical grids: extended indices of the lane's zone for the geometry tables (clamped:
   // lanes outside the grid compute but never store), the phi shift of a polar-axis ghost row,
   // inflow ghosts (flag bit 1) of the lane's column and of its outer neighbour
@@ -220,46 +165,44 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   const int zsh = (SPH && ((yf >> 2) & 1)) ? n2 / 2 : 0;
   const bool xinf = SPH && ((xf >> 1) & 1), xinfe = SPH && ((xef >> 1) & 1);
   // B of the lane's own zone (clamped into the domain so every lane may load it)
-  const int cbb = ((min(max(yz, 0), n1 - 1) * n0 + min(max(xz, 0), n0 - 1)) * G + g);
+  unsigned oz = (unsigned)((min(max(yz, 0), n1 - 1) * n0 + min(max(xz, 0), n0 - 1)) * G + g) * sizeof(S);
   // the wave's outer-row items: LDS slot and component (uniform), element offset within a
   // plane and flip of its row and column (per lane), the array (uniform)
-  int hslot[NHI], hcomp[NHI], hoff[NHI], hmask[NHI], hsh[NHI], hey[NHI];
+  int hslot[NHI], hcomp[NHI], hsh[NHI], hey[NHI];
+  unsigned hoff[NHI], hmask[NHI];
   const S* hsrc[NHI];
   for (int k = 0; k < NHI; ++k) {
-    int it = w + k * NI;
-    if (it >= NIT) it = -1;
-    int slot = 0, comp = 0;
-    if (it >= 0) {
-      if (it < 4) { slot = 0; comp = it; }
-      else if (it < 10) { slot = 1; comp = it - 4; }
-      else if (!AR || it < 16) { slot = NI + 2; comp = it - 10; }
-      else { slot = NI + 3; comp = it - 16; }
-    }
+    // (a wave short of an item repeats one: same value to the same place, and no branch)
+    const int it = (w + k * NI) % NIT;
+    int slot, comp;
+    if (it < 4) { slot = 0; comp = it; }
+    else if (it < 10) { slot = 1; comp = it - 4; }
+    else if (!AR || it < 16) { slot = NI + 2; comp = it - 10; }
+    else { slot = NI + 3; comp = it - 16; }
     int hys, hyf;
     c3_src(ax1, y0 - 2 + slot, hys, hyf);
-    hslot[k] = it >= 0 ? slot : -1;
+    hslot[k] = slot;
     hcomp[k] = comp;
-    hoff[k] = (hys * n0 + xs) * G + g;
-    const int hm = (xf & 1) | ((hyf & 1) << 1) | (((hyf >> 2) & 1) << 2);
-    hmask[k] = comp >= 1 && comp <= 3 ? ((hm >> (comp - 1)) & 1) : 0;
+    hoff[k] = (unsigned)((hys * n0 + xs) * G + g) * sizeof(S);
+    hmask[k] = comp == 1 ? sx : comp == 2 ? (unsigned)(hyf & 1) << 31 : comp == 3 ? (unsigned)((hyf >> 2) & 1) << 31 : 0u;
     hsh[k] = (SPH && ((hyf >> 2) & 1)) ? n2 / 2 : 0;
     hey[k] = min(max(y0 - 2 + slot, -2), n1 + 1) + NG;
     hsrc[k] = comp == 0 ? a.E : comp <= 3 ? a.F[comp - 1] : comp == 4 ? a.kap : a.sig;
   }
-  // plane m (-2 .. n2 + 1, clamped): element offset and flip mask
-  auto plane = [&](int m, int& pm) -> int {
+  // plane m (-2 .. n2 + 1, clamped): element offset and F_z's sign mask
+  auto plane = [&](int m, unsigned& pm) -> int64_t {
     int zs, zf;
     c3_src(ax2, m, zs, zf);
-    pm = (zf & 1) << 2;
-    return zs * PL;
+    pm = (unsigned)(zf & 1) << 31;
+    return (int64_t)zs * PL;
   };
   // plane m of a row shifted by sh in phi (a polar-axis ghost row: phi is periodic there)
-  auto plane_s = [&](int m, int sh, int& pm) -> int {
+  auto plane_s = [&](int m, int sh, unsigned& pm) -> int64_t {
     if (sh == 0) return plane(m, pm);
     pm = 0;
     int zz = (m + sh) % n2;
     if (zz < 0) zz += n2;
-    return zz * PL;
+    return (int64_t)zz * PL;
   };
   // the inflow ghost state of zone (extended ex_, ey_): E and covariant F_k = h_k F^_k with the
   // ghost's own scale factors (spherical grids, inflow on x1 only)
@@ -272,11 +215,13 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   };
 
   const bool want_diag = a.p_energy != nullptr;
-  ZoneDiag zd;
+  WaveDiag wd;
+  const unsigned long long updm = __builtin_amdgcn_ballot_w64(upd);
   const double cdt = a.c * a.dt;
   const R dtR = R(a.dt);
   const R idx0 = geo.idx[0], idx1 = geo.idx[1], idx2 = geo.idx[2];
-  const R dx0 = geo.dx[0], dx1 = geo.dx[1], dx2 = geo.dx[2];
+  const R dx1 = geo.dx[1], dx2 = geo.dx[2];
+  const R hdx0 = R(0.5) * geo.dx[0], hdx1 = R(0.5) * dx1, hdx2 = R(0.5) * dx2;
   const R hone[3] = {R(1), R(1), R(1)};
   const double Vz = want_diag ? (SPH ? geo.Wd[0][ex] * geo.Wd[1][ey] * geo.Wd[2][NG]
                                      : geo.Wd[0][NG] * geo.Wd[1][NG] * geo.Wd[2][NG])
@@ -316,6 +261,11 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
     }
   }
   auto rg = [&](int k) -> R { return RGT[SPH ? k : 0][x]; };
+  // eq:epsilon on z faces (zones of equal width along z)
+  auto eps_z = [&](R ksL, R ksR) -> R {
+    if constexpr (SPH) return epsilon_of(ksL, ksR, dlz, dlz);
+    else return epsilon_uniform(ksL, ksR, hdx2);
+  };
 
   // ---- register window along z: q(m), q(m + 1); the upper z face state of zone m and the
   // flux at m - 1/2; kappa and sigma of plane m ----
@@ -325,17 +275,18 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   // wave's outer-row items of plane m, kappa, sigma of m + 1 (Pk, Ps) and B of m (PB), all
   // loaded at the top of the plane before (Pk2, Ps2, PB2: those of the next plane)
   R Pr[4], Po[4], Ph[NHI], Pk, Ps, PB, Pk2, Ps2, PB2;
-  int Ppm, Popm;
+  unsigned y0m, y1m, y2m, y3m;   // F_z sign masks of planes m .. m + 3 (the lane's own row)
+  int64_t p1, p2, p3;            // element offsets of planes m + 1, m + 2, m + 3
+  FaceAux<R> xM{};               // |F^|^2 and cE of hiM
   // the wave's outer-row items of plane m (element offset off of the unshifted plane m)
-  auto load_items = [&](int off, int m) {
-    for (int k = 0; k < NHI; ++k)
-      if (hslot[k] >= 0) {
-        int o = off;
+  auto load_items = [&](int64_t off, int m) {
+    for (int k = 0; k < NHI; ++k) {
+        int64_t o = off;
         if (SPH && hsh[k] != 0) {
-          int pmx;
+          unsigned pmx;
           o = plane_s(m, hsh[k], pmx);
         }
-        Ph[k] = R(hsrc[k][o + hoff[k]]);
+        Ph[k] = R(ld_off(hsrc[k] + o, hoff[k]));
         if (SPH && xinf && hcomp[k] <= 3) {
           R qi[4];
           inflow_state(ex, hey[k], qi);
@@ -353,50 +304,49 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   const int64_t nfy = (int64_t)n0 * (n1 + 1) * n2, nfz = (int64_t)n0 * n1 * (n2 + 1);
   auto vel_z = [&](int f) -> R { return R(va.v[2][2 * nfz + ((int64_t)f * n1 + vyr) * n0 + vxz]); };
   R Ux = R(0), Uy = R(0), Uyt = R(0), Uz = R(0);   // face velocities of the plane
+  unsigned zm0;   // F_z sign mask of plane m (unshifted): the outer-row items'
   {
-    int pm;
+    unsigned ya, yb;
     R raw[4], qa[4], qb[4];
-    const int o0 = plane_s(mbeg, zsh, pm);
-    c3_load<S, R>(a, o0 + cb, raw);
-    c3_fix(raw, lm ^ pm, q0);
-    k0 = R(a.kap[o0 + cb]);
-    s0 = R(a.sig[o0 + cb]);
-    const int o1 = plane_s(mbeg + 1, zsh, pm);
-    c3_load<S, R>(a, o1 + cb, raw);
-    c3_fix(raw, lm ^ pm, q1);
-    int pa, pb;
-    const int oa = plane_s(mbeg - 2, zsh, pa), ob = plane_s(mbeg - 1, zsh, pb);
-    c3_load<S, R>(a, oa + cb, raw);
-    c3_fix(raw, lm ^ pa, qa);
-    c3_load<S, R>(a, ob + cb, raw);
-    c3_fix(raw, lm ^ pb, qb);
+    const int64_t p0 = plane_s(mbeg, zsh, y0m);
+    c3_load<S, R>(a, p0, ob, raw);
+    c3_fix(raw, sx, sy, sz ^ y0m, q0);
+    k0 = R(ld_off(a.kap + p0, ob));
+    s0 = R(ld_off(a.sig + p0, ob));
+    p1 = plane_s(mbeg + 1, zsh, y1m);
+    c3_load<S, R>(a, p1, ob, raw);
+    c3_fix(raw, sx, sy, sz ^ y1m, q1);
+    const int64_t pa = plane_s(mbeg - 2, zsh, ya), pb = plane_s(mbeg - 1, zsh, yb);
+    c3_load<S, R>(a, pa, ob, raw);
+    c3_fix(raw, sx, sy, sz ^ ya, qa);
+    c3_load<S, R>(a, pb, ob, raw);
+    c3_fix(raw, sx, sy, sz ^ yb, qb);
     if (SPH && xinf) {
       inflow_state(ex, ey, q0);
       inflow_state(ex, ey, q1);
       inflow_state(ex, ey, qa);
       inflow_state(ex, ey, qb);
     }
-    const R ksb = R(a.kap[ob + cb]) + R(a.sig[ob + cb]);
+    const R ksb = R(ld_off(a.kap + pb, ob)) + R(ld_off(a.sig + pb, ob));
     // face mbeg - 1/2 from zones mbeg - 1 (upper state) and mbeg (lower state)
     for (int c = 0; c < 4; ++c) hiM[c] = fPrev[c] = R(0);
     if (!idle) {
       R lo[4], hiP[4];
-      reconstruct<R, SPH, 3, LIM>(a, geo, 2, NG, qa, qb, q0, ihz, ihz, true, true, lo, hiP);
-      reconstruct<R, SPH, 3, LIM>(a, geo, 2, NG, qb, q0, q1, ihz, ihz, true, true, lo, hiM);
-      hll<R, SPH, 3, (LIM < 0)>(a, 2, hiP, lo, hz, ihz, epsilon_of(ksb, k0 + s0, dlz, dlz), fPrev);
+      FaceAux<R> xP, xl;
+      reconstruct<R, SPH, 3, LIM>(a, geo, 2, NG, qa, qb, q0, ihz, ihz, true, true, lo, hiP, nullptr, nullptr, &xP);
+      reconstruct<R, SPH, 3, LIM>(a, geo, 2, NG, qb, q0, q1, ihz, ihz, true, true, lo, hiM, nullptr, &xl, &xM);
+      hll<R, SPH, 3, (LIM < 0)>(a, 2, hiP, lo, hz, ihz, eps_z(ksb, k0 + s0), fPrev, &xP, &xl);
       if constexpr (VEL) add_upwind(vel_z(mbeg), hiP, lo, fPrev);
     }
     // in flight into the first plane
-    Pk = R(a.kap[o1 + cb]);
-    Ps = R(a.sig[o1 + cb]);
-    PB = R(a.B[mbeg * PL + cbb]);
-    const int o2 = plane_s(mbeg + 2, zsh, Ppm);
-    c3_load<S, R>(a, o2 + cb, Pr);
-    plane_s(mbeg, zsh, Popm);
-    c3_load<S, R>(a, o0 + ceb, Po);
+    Pk = R(ld_off(a.kap + p1, ob));
+    Ps = R(ld_off(a.sig + p1, ob));
+    PB = R(ld_off(a.B + (int64_t)mbeg * PL, oz));
+    p2 = plane_s(mbeg + 2, zsh, y2m);
+    c3_load<S, R>(a, p2, ob, Pr);
+    c3_load<S, R>(a, p0, oe, Po);
     if (SPH && xinfe) inflow_state(ex - 1, ey, Po);
-    int pmu;
-    load_items(plane(mbeg, pmu), mbeg);
+    load_items(plane(mbeg, zm0), mbeg);
   }
 
   // The update of plane m needs the y flux that the row above computes for plane m: it runs
@@ -404,112 +354,145 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   // the divergence and the flux at its lower y face, kappa, sigma, B).  With the LDS arrays
   // double-buffered by plane parity, the one barrier per plane orders every LDS access: a
   // buffer written for plane m was last read for plane m - 2, before the barrier of m - 1.
+  // (in double the state, the x and z part of the divergence, the lower y flux and the geometric
+  // source are kept as one value, U^n - dt (acc - f_y idx1) ..., a third of the registers; in
+  // float they stay apart, which fixes the order of the roundings.)
+  constexpr bool UA = sizeof(R) == 8;
+  // geometric source terms of the covariant flux components (cell-centred h), from the state qz
+  auto add_geometric = [&](const R qz[4], R U[4]) {
+    if constexpr (SPH) {
+      R h[3], ih[3], P[9], Sg[3];
+      h[0] = h[1] = rg(RG_HR);
+      h[2] = rg(RG_HR) * gld(geo.hs, ey);
+      ih[0] = ih[1] = rg(RG_IHR);
+      ih[2] = rg(RG_IHR) * gld(geo.ihs, ey);
+      closure_full<R, SPH, 3>(qz, ih, R(a.c), a.closure, P);
+      geometric_source<R>(P, h, ih, geo.gam + 4 * min(max(yz, 0), n1 - 1), R(a.c), Sg);
+      for (int cc = 0; cc < 3; ++cc) U[1 + cc] += dtR * Sg[cc];
+    } else {
+      (void)qz;
+      (void)U;
+    }
+  };
   R qU[4], accU[4], fyU[4], kU = R(0), sU = R(0), BU = R(0);
   for (int c = 0; c < 4; ++c) qU[c] = accU[c] = fyU[c] = R(0);
-  for (int m = mbeg; m <= mend; ++m) {
-    const int buf = m & 1;
-    const bool live = m < mend;       // the last pass only updates plane mend - 1
-    R q2[4], qo[4];
-    if (live) {
-      // ---- consume the values loaded one plane ago; the plane's rows to LDS ----
-      c3_fix(Pr, lm ^ Ppm, q2);            // plane m + 2
-      c3_fix(Po, lme ^ Popm, qo);          // outer x neighbour, plane m
-      if (SPH && xinf) inflow_state(ex, ey, q2);
-      if (SPH && xinfe) inflow_state(ex - 1, ey, qo);
-      for (int c = 0; c < 4; ++c) QS[buf][c][sw][lane] = q0[c];
-      QS[buf][4][sw][lane] = k0;
-      QS[buf][5][sw][lane] = s0;
-      for (int k = 0; k < NHI; ++k)
-        if (hslot[k] >= 0) {
-          const int zflip = (hcomp[k] == 3) ? (Popm >> 2) & 1 : 0;
-          QS[buf][hcomp[k]][hslot[k]][lane] = (hmask[k] ^ zflip) ? -Ph[k] : Ph[k];
-        }
-      // ---- loads for the next plane: q(m + 3), outer neighbours of m + 1, kappa, sigma of
-      // m + 2 and B of m + 1 (indices clamped into the ghost range; the last planes' are not
-      // used) ----
-      const int o3 = plane_s(min(m + 3, n2 + 1), zsh, Ppm);
-      c3_load<S, R>(a, o3 + cb, Pr);
-      const int oe = plane_s(min(m + 1, n2 + 1), zsh, Popm);
-      if (xedge) c3_load<S, R>(a, oe + ceb, Po);
-      int pmu;
-      load_items(SPH ? plane(min(m + 1, n2 + 1), pmu) : oe, min(m + 1, n2 + 1));
-      // kappa, sigma of m + 2 and B of m + 1 (they move into the window at the end of the plane:
-      // loaded here, a plane before, so that no wait for the loads in flight falls there)
-      const int ok = plane_s(min(m + 2, n2 + 1), zsh, pmu);
-      Pk2 = R(a.kap[ok + cb]);
-      Ps2 = R(a.sig[ok + cb]);
-      PB2 = R(a.B[min(m + 1, n2 - 1) * PL + cbb]);
-      if constexpr (VEL) {
-        // this plane's face velocities (used after the barrier)
-        Ux = R(va.v[0][((int64_t)m * n1 + vyr) * (n0 + 1) + vxc]);
-        Uy = R(va.v[1][nfy + ((int64_t)m * (n1 + 1) + vyf) * n0 + vxz]);
-        if (AR && top) Uyt = R(va.v[1][nfy + ((int64_t)m * (n1 + 1) + vyt) * n0 + vxz]);
-        Uz = vel_z(m + 1);
-      }
-    }
-    c3_barrier();
-    // ---- update of plane m - 1 (every lane of the inner rows computes; the lanes that hold a
-    // zone of the tile store) ----
-    if (m > mbeg && !idle) {
-      const int mu = m - 1;
+  const R dty = dtR * idx1;
+  // the update of plane mu from the kept values and the y flux that the row above computed for it
+  // (every lane of the inner rows computes; the lanes that hold a zone of the tile store); bu: the
+  // plane's LDS buffer
+  auto update = [&](const int mu, const int bu) {
+    const int64_t pu = (int64_t)mu * PL;
+    R Um[4];
+    if constexpr (UA) {
+      const R wh = SPH ? dtR * (gld(geo.wf[1], ey + 1) * gld(geo.iW[1], ey)) : dty;
+      for (int c = 0; c < 4; ++c) Um[c] = fma(-wh, FY[bu][c][w + 1][lane], qU[c]);
+    } else {
       R acc[4];
       if constexpr (SPH) {
         const R wl = gld(geo.wf[1], ey), wh = gld(geo.wf[1], ey + 1), iW = gld(geo.iW[1], ey);
-        for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (wh * FY[buf ^ 1][c][w + 1][lane] - wl * fyU[c]) * iW;
+        for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (wh * FY[bu][c][w + 1][lane] - wl * fyU[c]) * iW;
       } else {
-        for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (FY[buf ^ 1][c][w + 1][lane] - fyU[c]) * idx1;
+        for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (FY[bu][c][w + 1][lane] - fyU[c]) * idx1;
       }
-      const int zg = upd ? (mu * n1 + yz) * n0 * G + xz * G + g : 0;
-      R Um[4];
       for (int c = 0; c < 4; ++c) Um[c] = qU[c] - dtR * acc[c];
-      if constexpr (SPH) {
-        // geometric source terms of the covariant flux components (cell-centred h)
-        R h[3], ih[3], P[9], Sg[3];
-        h[0] = h[1] = rg(RG_HR);
-        h[2] = rg(RG_HR) * gld(geo.hs, ey);
-        ih[0] = ih[1] = rg(RG_IHR);
-        ih[2] = rg(RG_IHR) * gld(geo.ihs, ey);
-        closure_full<R, SPH, 3>(qU, ih, R(a.c), a.closure, P);
-        geometric_source<R>(P, h, ih, geo.gam + 4 * min(max(yz, 0), n1 - 1), R(a.c), Sg);
-        for (int cc = 0; cc < 3; ++cc) Um[1 + cc] += dtR * Sg[cc];
-      }
-      if (a.Ea) {
-        // second Runge-Kutta stage: U^- = (U^n + U* + dt L(U*)) / 2
-        Um[0] = R(0.5) * (R(a.Ea[zg]) + Um[0]);
-        for (int c = 0; c < 3; ++c) Um[1 + c] = R(0.5) * (R(a.Fa[c][zg]) + Um[1 + c]);
-      }
-      S Eo, F1[3];
-      double dz = 0.0;
-      if (a.src) {
-        const double ck = cdt * (double)kU;
-        dz = source_zone<S, R, SPH, 3>(a, geo, xz, yz, Um, ck, cdt * ((double)kU + (double)sU), ck * (double)BU,
-                                         want_diag && upd, Vz, zd, Eo, F1);
-      } else {
-        Eo = S(Um[0]);
-        for (int c = 0; c < 3; ++c) F1[c] = S(Um[1 + c]);
-      }
-      if (upd) {
-        a.Eo[zg] = Eo;
-        for (int c = 0; c < 3; ++c) a.Fo[c][zg] = F1[c];
-      }
-      if (a.dEm) {
-        // the zone's sum over the block's 4 groups (lanes 16 apart)
-        dz = upd ? dz : 0.0;
-        dz = lane_pair_sum<32>(lane_pair_sum<16>(dz));
-        if (upd && gq == 0) {
-          const int64_t zone = ((int64_t)mu * n1 + yz) * n0 + xz;
-          if (tl.ngb == 1) a.dEm[zone] = -dz;
-          else a.dzp[(int64_t)gb * a.nzones + zone] = dz;
+      if constexpr (SPH) add_geometric(qU, Um);
+    }
+    if (RK && a.Ea) {
+      // second Runge-Kutta stage: U^- = (U^n + U* + dt L(U*)) / 2
+      Um[0] = R(0.5) * (R(ld_off(a.Ea + pu, oz)) + Um[0]);
+      for (int c = 0; c < 3; ++c) Um[1 + c] = R(0.5) * (R(ld_off(a.Fa[c] + pu, oz)) + Um[1 + c]);
+    }
+    S Eo, F1[3];
+    double dz = 0.0;
+    if (a.src) {
+      const double ck = cdt * (double)kU;
+      dz = source_update<S, R, 3>(Um, ck, cdt * ((double)kU + (double)sU), ck * (double)BU, Eo, F1);
+      if (want_diag) {
+        double Fd[3] = {(double)F1[0], (double)F1[1], (double)F1[2]};
+        if constexpr (SPH) {
+          const double hd = (double)rg(RG_HR), hd2 = hd * (double)gld(geo.hs, ey);
+          const double ih = rcp_(hd);
+          Fd[0] *= ih;
+          Fd[1] *= ih;
+          Fd[2] *= rcp_(hd2);
         }
+        wave_diag<S, 3>(a.c, (double)Eo, Fd, updm, wd);
+      }
+    } else {
+      Eo = S(Um[0]);
+      for (int c = 0; c < 3; ++c) F1[c] = S(Um[1 + c]);
+    }
+    if (upd) {
+      st_off(a.Eo + pu, oz, Eo);
+      for (int c = 0; c < 3; ++c) st_off(a.Fo[c] + pu, oz, F1[c]);
+    }
+    if (a.dEm) {
+      // the zone's sum over the block's 4 groups (lanes 16 apart)
+      dz = upd ? dz : 0.0;
+      dz = lane_pair_sum<32>(lane_pair_sum<16>(dz));
+      if (upd && gq == 0) {
+        const int64_t zone = ((int64_t)mu * n1 + yz) * n0 + xz;
+        if (tl.ngb == 1) a.dEm[zone] = -dz;
+        else a.dzp[(int64_t)gb * a.nzones + zone] = dz;
       }
     }
-    if (!live) break;
+  };
+  for (int m = mbeg; m < mend; ++m) {
+    const int buf = m & 1;
+    R q2[4], qo[4], k1, s1, BM;
+    // (the offsets opaque to the compiler in each pass: their extension to 64 bits, hoisted out
+    // of the loop, would cost an address addition per access)
+    asm("" : "+v"(ob), "+v"(oe), "+v"(oz));
+    for (int k = 0; k < NHI; ++k) asm("" : "+v"(hoff[k]));
+    // ---- consume the values loaded one plane ago; the plane's rows to LDS ----
+    c3_fix(Pr, sx, sy, sz ^ y2m, q2);          // plane m + 2
+    c3_fix(Po, sxe, sy, sz ^ y0m, qo);         // outer x neighbour, plane m
+    k1 = Pk;
+    s1 = Ps;
+    BM = PB;
+    // (into registers of their own, so that the loads below can target the ones they came from:
+    // left to the compiler, the loads go elsewhere and are copied back before the barrier, where
+    // the copies wait for them)
+    for (int c = 0; c < 4; ++c) asm("" : "+v"(q2[c]), "+v"(qo[c]));
+    asm("" : "+v"(k1), "+v"(s1), "+v"(BM));
+    if (SPH && xinf) inflow_state(ex, ey, q2);
+    if (SPH && xinfe) inflow_state(ex - 1, ey, qo);
+    for (int c = 0; c < 4; ++c) QS[buf][c][sw][lane] = q0[c];
+    QS[buf][4][sw][lane] = k0;
+    QS[buf][5][sw][lane] = s0;
+    for (int k = 0; k < NHI; ++k)
+      QS[buf][hcomp[k]][hslot[k]][lane] = flip_sign(Ph[k], hmask[k] ^ (hcomp[k] == 3 ? zm0 : 0u));
+    // ---- loads for the next plane: q(m + 3), outer neighbours of m + 1, kappa, sigma of
+    // m + 2 and B of m + 1 (indices clamped into the ghost range; the last planes' are not
+    // used) ----
+    p3 = plane_s(min(m + 3, n2 + 1), zsh, y3m);
+    c3_load<S, R>(a, p3, ob, Pr);
+    if (xedge) c3_load<S, R>(a, p1, oe, Po);
+    if constexpr (SPH) {
+      load_items(plane(min(m + 1, n2 + 1), zm0), min(m + 1, n2 + 1));
+    } else {
+      load_items(p1, m + 1);
+      zm0 = y1m;
+    }
+    Pk = R(ld_off(a.kap + p2, ob));
+    Ps = R(ld_off(a.sig + p2, ob));
+    PB = R(ld_off(a.B + (int64_t)min(m + 1, n2 - 1) * PL, oz));
+    if constexpr (VEL) {
+      // this plane's face velocities (used after the barrier)
+      Ux = R(va.v[0][((int64_t)m * n1 + vyr) * (n0 + 1) + vxc]);
+      Uy = R(va.v[1][nfy + ((int64_t)m * (n1 + 1) + vyf) * n0 + vxz]);
+      if (AR && top) Uyt = R(va.v[1][nfy + ((int64_t)m * (n1 + 1) + vyt) * n0 + vxz]);
+      Uz = vel_z(m + 1);
+    }
+    c3_barrier();
+    if (m > mbeg && !idle) update(m - 1, buf ^ 1);
     const R ks0 = k0 + s0;
     // ---- y: the flux at the lower y face of the row, from the reconstructions of the row
     // below (upper state) and of the row (lower state) ----
     R fy[4];
     {
       R qa[4], qb[4], qc[4], lo[4], hiP[4], hiY[4], loY[4];
+      FaceAux<R> xP, xY, xYh;
       for (int c = 0; c < 4; ++c) {
         qa[c] = QS[buf][c][sw - 2][lane];
         qb[c] = QS[buf][c][sw - 1][lane];
@@ -535,13 +518,13 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
         ih_th(ey, ih0);
         ih_th(ey + 1, ih1);
         const bool om = gld(geo.wf[1], ey - 1) != R(0), o0f = gld(geo.wf[1], ey) != R(0), o1f = gld(geo.wf[1], ey + 1) != R(0);
-        reconstruct<R, SPH, 3, LIM>(a, geo, 1, ey - 1, qa, qb, q0, ihm, ih0, om, o0f, lo, hiP);
-        reconstruct<R, SPH, 3, LIM>(a, geo, 1, ey, qb, q0, qc, ih0, ih1, o0f, o1f, loY, hiY);
+        reconstruct<R, SPH, 3, LIM>(a, geo, 1, ey - 1, qa, qb, q0, ihm, ih0, om, o0f, lo, hiP, nullptr, nullptr, &xP);
+        reconstruct<R, SPH, 3, LIM>(a, geo, 1, ey, qb, q0, qc, ih0, ih1, o0f, o1f, loY, hiY, nullptr, &xY, &xYh);
         for (int c = 0; c < 4; ++c) fy[c] = R(0);
         if (o0f) {
           R hf[3];
           h_th(ey, hf);
-          hll<R, SPH, 3, (LIM < 0)>(a, 1, hiP, loY, hf, ih0, epsilon_of(ksb, ks0, dly, dly), fy);
+          hll<R, SPH, 3, (LIM < 0)>(a, 1, hiP, loY, hf, ih0, epsilon_of(ksb, ks0, dly, dly), fy, &xP, &xY);
         }
         if (AR && top && yz < n1) {
           // the block's upper face (ey + 1 <= n1 - 1 + NG + 1: inside the face tables)
@@ -550,27 +533,29 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
           const R ksa = QS[buf][4][sw + 1][lane] + QS[buf][5][sw + 1][lane];
           ih_th(ey + 2, ih2);
           const bool o2f = gld(geo.wf[1], ey + 2) != R(0);
-          reconstruct<R, SPH, 3, LIM>(a, geo, 1, ey + 1, q0, qc, qd, ih1, ih2, o1f, o2f, loA, hiA);
+          FaceAux<R> xA;
+          reconstruct<R, SPH, 3, LIM>(a, geo, 1, ey + 1, q0, qc, qd, ih1, ih2, o1f, o2f, loA, hiA, nullptr, &xA);
           for (int c = 0; c < 4; ++c) fu[c] = R(0);
           if (o1f) {
             R hf[3];
             h_th(ey + 1, hf);
-            hll<R, SPH, 3, (LIM < 0)>(a, 1, hiY, loA, hf, ih1, epsilon_of(ks0, ksa, dly, dly), fu);
+            hll<R, SPH, 3, (LIM < 0)>(a, 1, hiY, loA, hf, ih1, epsilon_of(ks0, ksa, dly, dly), fu, &xYh, &xA);
           }
           for (int c = 0; c < 4; ++c) FY[buf][c][NI][lane] = fu[c];
         }
       } else {
-        reconstruct<R, false, 3, LIM>(a, geo, 1, 0, qa, qb, q0, hone, hone, true, true, lo, hiP);
-        reconstruct<R, false, 3, LIM>(a, geo, 1, 0, qb, q0, qc, hone, hone, true, true, loY, hiY);
-        hll<R, false, 3, (LIM < 0)>(a, 1, hiP, loY, hone, hone, epsilon_of(ksb, ks0, dx1, dx1), fy);
+        reconstruct<R, false, 3, LIM>(a, geo, 1, 0, qa, qb, q0, hone, hone, true, true, lo, hiP, nullptr, nullptr, &xP);
+        reconstruct<R, false, 3, LIM>(a, geo, 1, 0, qb, q0, qc, hone, hone, true, true, loY, hiY, nullptr, &xY, &xYh);
+        hll<R, false, 3, (LIM < 0)>(a, 1, hiP, loY, hone, hone, epsilon_uniform(ksb, ks0, hdx1), fy, &xP, &xY);
         if constexpr (VEL) add_upwind(Uy, hiP, loY, fy);
         if (AR && top && yz < n1) {
           // the block's upper face
           R qd[4], loA[4], hiA[4], fu[4];
           for (int c = 0; c < 4; ++c) qd[c] = QS[buf][c][sw + 2][lane];
           const R ksa = QS[buf][4][sw + 1][lane] + QS[buf][5][sw + 1][lane];
-          reconstruct<R, false, 3, LIM>(a, geo, 1, 0, q0, qc, qd, hone, hone, true, true, loA, hiA);
-          hll<R, false, 3, (LIM < 0)>(a, 1, hiY, loA, hone, hone, epsilon_of(ks0, ksa, dx1, dx1), fu);
+          FaceAux<R> xA;
+          reconstruct<R, false, 3, LIM>(a, geo, 1, 0, q0, qc, qd, hone, hone, true, true, loA, hiA, nullptr, &xA);
+          hll<R, false, 3, (LIM < 0)>(a, 1, hiY, loA, hone, hone, epsilon_uniform(ks0, ksa, hdx1), fu, &xYh, &xA);
           if constexpr (VEL) add_upwind(Uyt, hiY, loA, fu);
           for (int c = 0; c < 4; ++c) FY[buf][c][NI][lane] = fu[c];
         }
@@ -584,11 +569,11 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
       {
         R qm[4], qp[4], loX[4], hiX[4];
         for (int c = 0; c < 4; ++c) {
-          const R pv = col_prev(q0[c]), nv = col_next(q0[c]);
-          qm[c] = x == 0 ? qo[c] : pv;
-          qp[c] = x == TX - 1 ? qo[c] : nv;
+          qm[c] = col_prev_or(q0[c], qo[c]);
+          qp[c] = col_next_or(q0[c], qo[c]);
         }
         R qL[4], fx[4];
+        FaceAux<R> xX, xXh, xL;
         if constexpr (SPH) {
           // r faces of the lane's zone; the flux at its lower face
           R ihl[3], ihr[3], hf[3];
@@ -598,21 +583,25 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
           ihr[0] = ihr[1] = rg(RG_IRF1);
           ihr[2] = rg(RG_IRF1) * isc;
           const R vs[5] = {rg(RG_IDM), rg(RG_IDP), rg(RG_DLO), rg(RG_DHI), rg(RG_IDC)};
-          reconstruct<R, SPH, 3, LIM>(a, geo, 0, ex, qm, q0, qp, ihl, ihr, true, true, loX, hiX, vs);
+          reconstruct<R, SPH, 3, LIM>(a, geo, 0, ex, qm, q0, qp, ihl, ihr, true, true, loX, hiX, vs, &xX, &xXh);
           for (int c = 0; c < 4; ++c) qL[c] = col_prev(hiX[c]);
           const R ksL = col_prev(ks0);
           const R dlx = rg(RG_HR) * geo.dx[0];
           const R dlL = col_prev(dlx);
           hf[0] = hf[1] = rg(RG_RF);
           hf[2] = rg(RG_RF) * gld(geo.sc, ey);
-          hll<R, SPH, 3, (LIM < 0)>(a, 0, qL, loX, hf, ihl, epsilon_of(ksL, ks0, dlL, dlx), fx);
+          xL.F2 = col_prev(xXh.F2);
+          xL.X = R(a.c) * qL[0];
+          hll<R, SPH, 3, (LIM < 0)>(a, 0, qL, loX, hf, ihl, epsilon_of(ksL, ks0, dlL, dlx), fx, &xL, &xX);
           const R wl = rg(RG_WF0), wh = rg(RG_WF1), iW = rg(RG_IW);
           for (int c = 0; c < 4; ++c) acc[c] = (wh * col_next(fx[c]) - wl * fx[c]) * iW;
         } else {
-          reconstruct<R, false, 3, LIM>(a, geo, 0, 0, qm, q0, qp, hone, hone, true, true, loX, hiX);
+          reconstruct<R, false, 3, LIM>(a, geo, 0, 0, qm, q0, qp, hone, hone, true, true, loX, hiX, nullptr, &xX, &xXh);
           for (int c = 0; c < 4; ++c) qL[c] = col_prev(hiX[c]);
           const R ksL = col_prev(ks0);
-          hll<R, false, 3, (LIM < 0)>(a, 0, qL, loX, hone, hone, epsilon_of(ksL, ks0, dx0, dx0), fx);
+          xL.F2 = col_prev(xXh.F2);
+          xL.X = R(a.c) * qL[0];
+          hll<R, false, 3, (LIM < 0)>(a, 0, qL, loX, hone, hone, epsilon_uniform(ksL, ks0, hdx0), fx, &xL, &xX);
           if constexpr (VEL) add_upwind(Ux, qL, loX, fx);
           for (int c = 0; c < 4; ++c) acc[c] = (col_next(fx[c]) - fx[c]) * idx0;
         }
@@ -621,8 +610,10 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
       // move on at once ----
       {
         R nLo[4], nHi[4], fNext[4];
-        reconstruct<R, SPH, 3, LIM>(a, geo, 2, NG, q0, q1, q2, ihz, ihz, true, true, nLo, nHi);
-        hll<R, SPH, 3, (LIM < 0)>(a, 2, hiM, nLo, hz, ihz, epsilon_of(ks0, Pk + Ps, dlz, dlz), fNext);
+        FaceAux<R> xl, xh;
+        reconstruct<R, SPH, 3, LIM>(a, geo, 2, NG, q0, q1, q2, ihz, ihz, true, true, nLo, nHi, nullptr, &xl, &xh);
+        hll<R, SPH, 3, (LIM < 0)>(a, 2, hiM, nLo, hz, ihz, eps_z(ks0, k1 + s1), fNext, &xM, &xl);
+        xM = xh;
         if constexpr (VEL) add_upwind(Uz, hiM, nLo, fNext);
         for (int c = 0; c < 4; ++c) {
           acc[c] += (fNext[c] - fPrev[c]) * idx2;
@@ -632,54 +623,36 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
       }
     }
     // ---- keep what the update of plane m needs; advance the window ----
+    if constexpr (UA) {
+      const R wl = SPH ? gld(geo.wf[1], ey) * gld(geo.iW[1], ey) : idx1;
+      for (int c = 0; c < 4; ++c) qU[c] = q0[c] - dtR * (acc[c] - fy[c] * wl);
+      add_geometric(q0, qU);
+    }
     for (int c = 0; c < 4; ++c) {
-      qU[c] = q0[c];
-      accU[c] = acc[c];
-      fyU[c] = fy[c];
+      if constexpr (!UA) {
+        qU[c] = q0[c];
+        accU[c] = acc[c];
+        fyU[c] = fy[c];
+      }
       q0[c] = q1[c];
       q1[c] = q2[c];
     }
     kU = k0;
     sU = s0;
-    BU = PB;
-    k0 = Pk;
-    s0 = Ps;
-    Pk = Pk2;
-    Ps = Ps2;
-    PB = PB2;
+    BU = BM;
+    k0 = k1;
+    s0 = s1;
+    p1 = p2;
+    p2 = p3;
+    y0m = y1m;
+    y1m = y2m;
+    y2m = y3m;
   }
+  c3_barrier();
+  if (!idle) update(mend - 1, (mend - 1) & 1);
 
-  if (!want_diag) return;
-  // ---- block partials of the diagnostics ----
-  double e = zd.energy, mf = zd.maxf2();
-  int un = zd.nun, pnp = zd.nnp;
-  for (int off = 32; off > 0; off >>= 1) {
-    e += __shfl_xor(e, off);
-    mf = fmax(mf, __shfl_xor(mf, off));
-    un += __shfl_xor(un, off);
-    pnp += __shfl_xor(pnp, off);
-  }
-  if (lane == 0) {
-    red_e[w] = e;
-    red_m[w] = mf;
-    red_u[w] = un;
-    red_p[w] = pnp;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double se = 0.0, sm = 0.0;
-    int su = 0, sp = 0;
-    for (int k = 0; k < NI; ++k) {
-      se += red_e[k];
-      sm = fmax(sm, red_m[k]);
-      su += red_u[k];
-      sp += red_p[k];
-    }
-    a.p_energy[blockIdx.x] = se;
-    a.p_maxf2[blockIdx.x] = sm;
-    a.p_nun[blockIdx.x] = su;
-    a.p_nnp[blockIdx.x] = sp;
-  }
+  if (want_diag)
+    wave_diag_store(wd, upd, Vz, w, lane, NI, red_e, red_m, red_u, red_p, a.p_energy, a.p_maxf2, a.p_nun, a.p_nnp);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -780,8 +753,12 @@ int launch_c3(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, hipSt
   const VelArgs<S> nova{};
 #define FM1_C3(NRV, WV, SP, AR)                                                                                       \
   do {                                                                                                                \
-    if (mm)                                                                                                           \
-      hipLaunchKernelGGL((k_step_3d<S, NRV, WV, FORNAX_LIMITER_MINMOD, SP, AR>), grid, block, 0, st, a, geo, tl, nova); \
+    if (mm && !a.Ea)                                                                                                  \
+      hipLaunchKernelGGL((k_step_3d<S, NRV, WV, FORNAX_LIMITER_MINMOD, SP, AR, false, false>), grid, block, 0, st, a,  \
+                         geo, tl, nova);                                                                              \
+    else if (mm)                                                                                                      \
+      hipLaunchKernelGGL((k_step_3d<S, NRV, WV, FORNAX_LIMITER_MINMOD, SP, AR, false, true>), grid, block, 0, st, a,   \
+                         geo, tl, nova);                                                                              \
     else                                                                                                              \
       hipLaunchKernelGGL((k_step_3d<S, NRV, WV, -1, SP, AR>), grid, block, 0, st, a, geo, tl, nova);                    \
   } while (0)
@@ -827,10 +804,10 @@ int launch_c3_vel(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, c
   const bool mm = a.limiter == FORNAX_LIMITER_MINMOD && a.wavespeed == FORNAX_WAVESPEED_LIGHT;
   dim3 grid(tl.nblocks), block(64 * tl.NR);
   if (mm)
-    hipLaunchKernelGGL((k_step_3d<S, NRV, WV, FORNAX_LIMITER_MINMOD, false, true, true>), grid, block, 0, st, a, geo, tl,
+    hipLaunchKernelGGL((k_step_3d<S, NRV, WV, FORNAX_LIMITER_MINMOD, false, true, true, false>), grid, block, 0, st, a, geo, tl,
                        va);
   else
-    hipLaunchKernelGGL((k_step_3d<S, NRV, WV, -1, false, true, true>), grid, block, 0, st, a, geo, tl, va);
+    hipLaunchKernelGGL((k_step_3d<S, NRV, WV, -1, false, true, true, false>), grid, block, 0, st, a, geo, tl, va);
   return hipGetLastError() == hipSuccess ? FORNAX_OK : FORNAX_EDEVICE;
 }
 
