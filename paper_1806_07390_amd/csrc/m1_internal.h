@@ -173,11 +173,11 @@ struct Tile {
   int nthreads;        // 64 NW (1-D/2-D) or TXB * TYB * GB (3-D)
   size_t lds;          // dynamic LDS bytes per block (with the dE_matter buffer)
 };
-// Tiling of the 3-D Cartesian step kernel for group counts that are multiples of 4
-// (m1_step_3d.hip): blocks of NR waves, one y row of 16 x columns by 4 groups each (rows 0 and
-// NR - 1 and columns 0 and 15 are halo), TM planes along z, ngb = G / 4 blocks per tile.
+// Tiling of the 3-D step kernel (m1_step_3d.hip): blocks of NR waves, one y row of 16 x columns by
+// 4 groups each (columns 0 and 15 are halo), or with one or two groups of RT = 4 or 2 x tiles by
+// all groups; TM planes along z; ngb = ceil(G / 4) blocks per tile; ntx blocks along x.
 struct C3Tile {
-  int NR, TM;
+  int NR, TM, RT;
   int ntx, nty, ntz, ngb, nblocks;
   int xq, xr;
 };

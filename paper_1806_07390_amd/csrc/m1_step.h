@@ -31,8 +31,8 @@ template <typename S>
 int launch_rows(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, hipStream_t st);
 
 // The 3-D kernel with x neighbours by lane shifts and y neighbours through LDS
-// (m1_step_3d.hip): a tile with nblocks = 0 when the grid does not qualify (3-D, groups a
-// multiple of 4; Cartesian without inflow or axis boundaries, or spherical with inflow at the
+// (m1_step_3d.hip): a tile with nblocks = 0 when the grid does not qualify (3-D;
+// Cartesian without inflow or axis boundaries, or spherical with inflow at the
 // inner radius and polar axes over a periodic phi of even length; NR 6, 8 or 12 in double,
 // 4, 8 or 16 in float, 8 (double) or 4, 8 and 12 (float) on spherical grids).
 C3Tile make_c3_tile(const fornax_m1_desc& D, int NR, int TM);

@@ -1,11 +1,12 @@
-// m1_step_3d.hip -- the fused M1 step for 3-D grids whose group count is a multiple of 4: the
-// Cartesian 192^3 x 12 workload's layout, and spherical (ln r, theta, phi) grids with an inflow
+// m1_step_3d.hip -- the fused M1 step for 3-D grids: the Cartesian 192^3 x 12 workload's layout, and spherical (ln r, theta, phi) grids with an inflow
 // inner boundary, polar axes and periodic phi (the 256 x 64 x 128 x 20 workload).
 //
 // Same method and arithmetic as k_step_tiled (eq:finite_vol with the reconstruction of
 // eq:recon_constraints, the M1 closure, the HLL flux eq:hll with the correction eq:epsilon, the
 // backward-Euler interaction update eq:be_update); what differs is how neighbours meet:
-//   * a wave is one y row of 16 x columns by 4 consecutive groups, lane = 16 group + column:
+//   * a wave is one y row of 16 x columns by 4 consecutive groups, lane = 16 group + column (with
+//     one or two groups: of four or two x tiles, each with all its groups; rows past the last
+//     group idle):
 //     the x neighbours of a lane are the lanes next to it in its 16-lane row, reached by DPP
 //     row shifts (no LDS, no barrier).  Columns 0 and 15 are halo: their zones are
 //     reconstructed (their face states close the tile) but not updated, and their own outer
@@ -133,12 +134,18 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   const int tz = rest / tl.nty;
 
   const int n0 = a.n[0], n1 = a.n[1], n2 = a.n[2], G = a.G;
-  const int g = gb * 4 + gq;
-  const int xz = tx * (TX - 2) + x - 1;          // zone of the lane's column
+  // the row's group and x tile: four groups of one tile, or with one or two groups all groups of
+  // RT = 4 or 2 tiles; lanes past the last group repeat it (they never store)
+  // (in float the group count is a multiple of 4)
+  const int RT = sizeof(R) == 8 ? tl.RT : 1;
+  const int g = RT == 1 ? gb * 4 + gq : (G == 2 ? gq & 1 : 0);
+  const int gc = sizeof(R) == 8 ? min(g, G - 1) : g;
+  const int xt = RT == 1 ? tx : tx * RT + (G == 2 ? gq >> 1 : gq);
+  const int xz = xt * (TX - 2) + x - 1;          // zone of the lane's column
   const int y0 = ty * (AR ? NI : NI - 1);        // zone of slot 2
   const int yz = y0 + w;                         // zone of the wave's row
   const int mbeg = tz * tl.TM, mend = min(mbeg + tl.TM, n2);
-  const bool upd = !idle && yz < n1 && x >= 1 && x <= TX - 2 && xz < n0;
+  const bool upd = !idle && yz < n1 && x >= 1 && x <= TX - 2 && xz < n0 && (sizeof(R) == 4 || g < G);
   const int PL = n0 * n1 * G;                    // elements of a z plane
 
   const C3Axis ax0 = c3_axis<0>(a), ax1 = c3_axis<1>(a), ax2 = c3_axis<2>(a);
@@ -149,10 +156,10 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   const bool xedge = x == 0 || x == TX - 1;
   int xef;
   // byte offsets within a plane (below 2^32: a grid has fewer than 2^29 zone-groups)
-  unsigned ob = (unsigned)((ys * n0 + xs) * G + g) * sizeof(S);
+  unsigned ob = (unsigned)((ys * n0 + xs) * G + gc) * sizeof(S);
   int xeo;
   c3_src(ax0, x == 0 ? xz - 1 : xz + 1, xeo, xef);
-  unsigned oe = (unsigned)((ys * n0 + xeo) * G + g) * sizeof(S);
+  unsigned oe = (unsigned)((ys * n0 + xeo) * G + gc) * sizeof(S);
   // sign masks: F_x flips in reflected columns, F_y in reflected or polar-axis rows, F_z in
   // polar-axis rows (flag bit 2) and in reflected planes
   const unsigned sx = (unsigned)(xf & 1) << 31, sxe = (unsigned)(xef & 1) << 31;
@@ -165,7 +172,7 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   const int zsh = (SPH && ((yf >> 2) & 1)) ? n2 / 2 : 0;
   const bool xinf = SPH && ((xf >> 1) & 1), xinfe = SPH && ((xef >> 1) & 1);
   // B of the lane's own zone (clamped into the domain so every lane may load it)
-  unsigned oz = (unsigned)((min(max(yz, 0), n1 - 1) * n0 + min(max(xz, 0), n0 - 1)) * G + g) * sizeof(S);
+  unsigned oz = (unsigned)((min(max(yz, 0), n1 - 1) * n0 + min(max(xz, 0), n0 - 1)) * G + gc) * sizeof(S);
   // the wave's outer-row items: LDS slot and component (uniform), element offset within a
   // plane and flip of its row and column (per lane), the array (uniform)
   int hslot[NHI], hcomp[NHI], hsh[NHI], hey[NHI];
@@ -183,7 +190,7 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
     c3_src(ax1, y0 - 2 + slot, hys, hyf);
     hslot[k] = slot;
     hcomp[k] = comp;
-    hoff[k] = (unsigned)((hys * n0 + xs) * G + g) * sizeof(S);
+    hoff[k] = (unsigned)((hys * n0 + xs) * G + gc) * sizeof(S);
     hmask[k] = comp == 1 ? sx : comp == 2 ? (unsigned)(hyf & 1) << 31 : comp == 3 ? (unsigned)((hyf >> 2) & 1) << 31 : 0u;
     hsh[k] = (SPH && ((hyf >> 2) & 1)) ? n2 / 2 : 0;
     hey[k] = min(max(y0 - 2 + slot, -2), n1 + 1) + NG;
@@ -207,7 +214,7 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   // the inflow ghost state of zone (extended ex_, ey_): E and covariant F_k = h_k F^_k with the
   // ghost's own scale factors (spherical grids, inflow on x1 only)
   auto inflow_state = [&](int ex_, int ey_, R q[4]) {
-    const double* in = a.inflow + g * 4;
+    const double* in = a.inflow + gc * 4;
     R h[3];
     cell_h<R, SPH>(geo, ex_, ey_, h);
     q[0] = R(in[0]);
@@ -240,27 +247,28 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   // tables (the theta tables, indexed by the wave's row, are scalar loads)
   enum { RG_IRC, RG_RC, RG_HR, RG_IHR, RG_IRF0, RG_IRF1, RG_RF, RG_IDM, RG_IDP, RG_DLO, RG_DHI, RG_IDC, RG_WF0,
          RG_WF1, RG_IW, RG_N };
-  __shared__ R RGT[SPH ? RG_N : 1][TX];
+  __shared__ R RGT[SPH ? RG_N : 1][sizeof(R) == 8 ? 64 : TX];
+  const int xl = RT == 1 ? x : lane;          // the column's entry (rows share a tile, or not)
   if constexpr (SPH) {
-    if (w == 0 && gq == 0) {
-      RGT[RG_IRC][x] = gld(geo.irc, ex);
-      RGT[RG_RC][x] = gld(geo.rc, ex);
-      RGT[RG_HR][x] = gld(geo.hr, ex);
-      RGT[RG_IHR][x] = gld(geo.ihr, ex);
-      RGT[RG_IRF0][x] = gld(geo.irf, ex);
-      RGT[RG_IRF1][x] = gld(geo.irf, ex + 1);
-      RGT[RG_RF][x] = gld(geo.rf, ex);
-      RGT[RG_IDM][x] = gld(geo.idm[0], ex);
-      RGT[RG_IDP][x] = gld(geo.idp[0], ex);
-      RGT[RG_DLO][x] = gld(geo.dlo[0], ex);
-      RGT[RG_DHI][x] = gld(geo.dhi[0], ex);
-      RGT[RG_IDC][x] = gld(geo.idc[0], ex);
-      RGT[RG_WF0][x] = gld(geo.wf[0], ex);
-      RGT[RG_WF1][x] = gld(geo.wf[0], ex + 1);
-      RGT[RG_IW][x] = gld(geo.iW[0], ex);
+    if (w == 0 && xl == lane) {
+      RGT[RG_IRC][xl] = gld(geo.irc, ex);
+      RGT[RG_RC][xl] = gld(geo.rc, ex);
+      RGT[RG_HR][xl] = gld(geo.hr, ex);
+      RGT[RG_IHR][xl] = gld(geo.ihr, ex);
+      RGT[RG_IRF0][xl] = gld(geo.irf, ex);
+      RGT[RG_IRF1][xl] = gld(geo.irf, ex + 1);
+      RGT[RG_RF][xl] = gld(geo.rf, ex);
+      RGT[RG_IDM][xl] = gld(geo.idm[0], ex);
+      RGT[RG_IDP][xl] = gld(geo.idp[0], ex);
+      RGT[RG_DLO][xl] = gld(geo.dlo[0], ex);
+      RGT[RG_DHI][xl] = gld(geo.dhi[0], ex);
+      RGT[RG_IDC][xl] = gld(geo.idc[0], ex);
+      RGT[RG_WF0][xl] = gld(geo.wf[0], ex);
+      RGT[RG_WF1][xl] = gld(geo.wf[0], ex + 1);
+      RGT[RG_IW][xl] = gld(geo.iW[0], ex);
     }
   }
-  auto rg = [&](int k) -> R { return RGT[SPH ? k : 0][x]; };
+  auto rg = [&](int k) -> R { return RGT[SPH ? k : 0][xl]; };
   // eq:epsilon on z faces (zones of equal width along z)
   auto eps_z = [&](R ksL, R ksR) -> R {
     if constexpr (SPH) return epsilon_of(ksL, ksR, dlz, dlz);
@@ -427,10 +435,11 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
       for (int c = 0; c < 3; ++c) st_off(a.Fo[c] + pu, oz, F1[c]);
     }
     if (a.dEm) {
-      // the zone's sum over the block's 4 groups (lanes 16 apart)
+      // the zone's sum over the rows that hold its groups (lanes 16 apart)
       dz = upd ? dz : 0.0;
-      dz = lane_pair_sum<32>(lane_pair_sum<16>(dz));
-      if (upd && gq == 0) {
+      if (RT < 4) dz = lane_pair_sum<16>(dz);
+      if (RT < 2) dz = lane_pair_sum<32>(dz);
+      if (upd && g == gb * 4) {
         const int64_t zone = ((int64_t)mu * n1 + yz) * n0 + xz;
         if (tl.ngb == 1) a.dEm[zone] = -dz;
         else a.dzp[(int64_t)gb * a.nzones + zone] = dz;
@@ -525,6 +534,7 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
           R hf[3];
           h_th(ey, hf);
           hll<R, SPH, 3, (LIM < 0)>(a, 1, hiP, loY, hf, ih0, epsilon_of(ksb, ks0, dly, dly), fy, &xP, &xY);
+          if constexpr (VEL) add_upwind(Uy, hiP, loY, fy);
         }
         if (AR && top && yz < n1) {
           // the block's upper face (ey + 1 <= n1 - 1 + NG + 1: inside the face tables)
@@ -540,6 +550,7 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
             R hf[3];
             h_th(ey + 1, hf);
             hll<R, SPH, 3, (LIM < 0)>(a, 1, hiY, loA, hf, ih1, epsilon_of(ks0, ksa, dly, dly), fu, &xYh, &xA);
+            if constexpr (VEL) add_upwind(Uyt, hiY, loA, fu);
           }
           for (int c = 0; c < 4; ++c) FY[buf][c][NI][lane] = fu[c];
         }
@@ -593,6 +604,7 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
           xL.F2 = col_prev(xXh.F2);
           xL.X = R(a.c) * qL[0];
           hll<R, SPH, 3, (LIM < 0)>(a, 0, qL, loX, hf, ihl, epsilon_of(ksL, ks0, dlL, dlx), fx, &xL, &xX);
+          if constexpr (VEL) add_upwind(Ux, qL, loX, fx);
           const R wl = rg(RG_WF0), wh = rg(RG_WF1), iW = rg(RG_IW);
           for (int c = 0; c < 4; ++c) acc[c] = (wh * col_next(fx[c]) - wl * fx[c]) * iW;
         } else {
@@ -663,7 +675,7 @@ static bool c3_all_rows(const fornax_m1_desc& D, int NR) { return D.precision ==
 C3Tile make_c3_tile(const fornax_m1_desc& D, int NR, int TM) {
   C3Tile tl{};
   tl.nblocks = 0;
-  if (D.ndim != 3 || D.ngroups % 4 != 0) return tl;
+  if (D.ndim != 3 || (D.precision != FORNAX_FP64 && D.ngroups % 4 != 0)) return tl;
   const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
   if (!sph && D.coord != FORNAX_CARTESIAN) return tl;
   // the instantiated block heights: 6, 8 or 12 rows in double, 4, 8, 12 or 16 in float
@@ -683,11 +695,12 @@ C3Tile make_c3_tile(const fornax_m1_desc& D, int NR, int TM) {
     return tl;
   tl.NR = NR;
   tl.TM = TM;
-  tl.ntx = (D.n[0] + C3_TX - 3) / (C3_TX - 2);
+  tl.RT = D.ngroups == 1 ? 4 : (D.ngroups == 2 ? 2 : 1);
+  tl.ntx = ((D.n[0] + C3_TX - 3) / (C3_TX - 2) + tl.RT - 1) / tl.RT;
   // tiles of NR rows, or NR - 1 (the top row is the next tile's first)
   tl.nty = c3_all_rows(D, NR) ? (D.n[1] + NR - 1) / NR : (D.n[1] + NR - 2) / (NR - 1);
   tl.ntz = (D.n[2] + TM - 1) / TM;
-  tl.ngb = D.ngroups / 4;
+  tl.ngb = (D.ngroups + 3) / 4;
   const int64_t nb = (int64_t)tl.ntx * tl.nty * tl.ntz * tl.ngb;
   if (nb > (int64_t)1 << 30) return C3Tile{};
   tl.nblocks = (int)nb;
@@ -730,6 +743,12 @@ C3Tile choose_c3_tile(const fornax_m1_desc& D, int cus) {
   // double 2, float Cartesian 4, float spherical 3.
   const bool dbl = D.precision == FORNAX_FP64;
   const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
+  // Group counts that leave rows idle (5 groups: 3 of 8) still run 1.2 to 2.3 times faster here
+  // than on the tiled kernel in double (1, 2, 3, 5, 6, 7, 9 and 10 groups, Cartesian 90 x 70 x 60
+  // and 180 x 160 x 150, spherical 96 x 32 x 48 and 256 x 64 x 128).  In float they keep the tiled
+  // kernel (make_c3_tile refuses them), and its results bit for bit: it adds the three directions
+  // in another order, and the float roundings of a step show in its double diagnostics and steer
+  // the limiter of the next.
   return c3_tile_by_rounds(D, (sph && !dbl) ? 12 : 8, dbl ? 2 : (sph ? 3 : 4), cus);
 }
 
@@ -737,7 +756,15 @@ C3Tile choose_c3_tile(const fornax_m1_desc& D, int cus) {
 // float (launch_c3_vel)
 C3Tile choose_c3_vel_tile(const fornax_m1_desc& D, int cus) {
   const bool dbl = D.precision == FORNAX_FP64;
-  if (D.coord != FORNAX_CARTESIAN) return C3Tile{};
+  // in float the grids whose Step 1 runs here, and no others (see choose_c3_tile)
+  const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
+  if (!dbl && sph) return C3Tile{};
+  // spherical grids, and group counts that leave rows idle, from the size on where the blocks
+  // fill the chip; below it one thread per zone-group is faster (measured in double: spherical
+  // 32 x 8 x 8 x 12 80 against 49 us, 64 x 16 x 24 x 6 105 against 99, 160 x 48 x 80 x 3 276 against
+  // 475; Cartesian 20^3 x 3 55 against 42, 40 x 30 x 30 x 3 72 against 71, 144^3 x 3 791 against 1608)
+  const int64_t nzg = (int64_t)D.n[0] * D.n[1] * D.n[2] * D.ngroups;
+  if ((sph && nzg < (1 << 18)) || (D.ngroups % 4 != 0 && nzg < (1 << 17))) return C3Tile{};
   return c3_tile_by_rounds(D, dbl ? 8 : 12, dbl ? 2 : 3, cus);
 }
 
@@ -795,7 +822,7 @@ template int launch_c3<float>(fornax_m1_ctx*, const Geo<float>&, const StepArgs<
 template <typename S>
 int launch_c3_vel(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, const VelArgs<S>& va, hipStream_t st) {
   const fornax_m1_desc& D = ctx->desc;
-  if (D.coord != FORNAX_CARTESIAN || D.ndim != 3) return FORNAX_EUNSUPPORTED;
+  if (D.ndim != 3) return FORNAX_EUNSUPPORTED;
   if (a.src || a.dEm || a.p_energy || a.Ea) return FORNAX_EUNSUPPORTED;
   constexpr bool dbl = sizeof(S) == 8;
   const C3Tile tl = ctx->c3v;
@@ -803,11 +830,17 @@ int launch_c3_vel(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, c
   if (tl.nblocks <= 0 || tl.NR != NRV) return FORNAX_EUNSUPPORTED;
   const bool mm = a.limiter == FORNAX_LIMITER_MINMOD && a.wavespeed == FORNAX_WAVESPEED_LIGHT;
   dim3 grid(tl.nblocks), block(64 * tl.NR);
-  if (mm)
-    hipLaunchKernelGGL((k_step_3d<S, NRV, WV, FORNAX_LIMITER_MINMOD, false, true, true, false>), grid, block, 0, st, a, geo, tl,
-                       va);
-  else
-    hipLaunchKernelGGL((k_step_3d<S, NRV, WV, -1, false, true, true, false>), grid, block, 0, st, a, geo, tl, va);
+  if (!dbl && D.coord == FORNAX_SPHERICAL_LOGR) return FORNAX_EUNSUPPORTED;
+#define FM1_C3V(LIMV, SP) \
+  hipLaunchKernelGGL((k_step_3d<S, NRV, WV, LIMV, SP, true, true, false>), grid, block, 0, st, a, geo, tl, va)
+  const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
+  if constexpr (dbl) {
+    if (mm && sph) FM1_C3V(FORNAX_LIMITER_MINMOD, true);
+    else if (sph) FM1_C3V(-1, true);
+  }
+  if (!sph && mm) FM1_C3V(FORNAX_LIMITER_MINMOD, false);
+  else if (!sph) FM1_C3V(-1, false);
+#undef FM1_C3V
   return hipGetLastError() == hipSuccess ? FORNAX_OK : FORNAX_EDEVICE;
 }
 

@@ -10,8 +10,9 @@
 //                   of the reconstructed face states, geometric sources) plus v^d U_upwind on
 //                   every face and, in the flux rows, + <Gamma^l_{ik}> <v^i> F_l - <v^i_{;k}> F_i;
 //                   writes U^(1) to the output state;
-//                   On 3-D Cartesian grids of the whole-zone 3-D kernel's kind (groups a multiple
-//                   of 4) Step 1 runs on that kernel instead (m1_step_3d.hip: the transport with
+//                   On 3-D grids of the 3-D kernel's kind (choose_c3_vel_tile: in double but for
+//                   small grids, in float Cartesian with groups a multiple of 4)
+//                   Step 1 runs on that kernel instead (m1_step_3d.hip: the transport with
 //                   the advective fluxes), and the zone-local velocity terms of the flux rows
 //                   move to k_vel_freq, which reads F^n for them;
 //   k_vel_freq      whole zones per block (BLOCK / G zones of G groups, lanes = groups): Step 2
@@ -496,7 +497,7 @@ int launch_vel_nd(fornax_m1_ctx* ctx, const Geo<R>& geo, StepArgs<S>& a, const V
                   const fornax_m1_diag* diag, hipStream_t st) {
   VelArgs<S> vf = va;
   bool fused = false;
-  if constexpr (!SPH && ND == 3 && std::is_same<S, R>::value) {
+  if constexpr (ND == 3 && std::is_same<S, R>::value) {
     // Step 1 on the whole-zone 3-D kernel where the grid is of its kind: transport with the
     // advective fluxes; the flux rows' zone-local velocity terms move to the frequency step
     StepArgs<S> s1 = a;
