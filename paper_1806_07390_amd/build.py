@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libfornax_m1.so")
 SOURCES = ["m1_host.cpp", "m1_kernels.hip", "m1_step.hip", "m1_step_rows.hip", "m1_step_3d.hip", "m1_adjoint.hip",
-           "m1_matter.hip", "m1_velocity.hip"]
+           "m1_matter.hip", "m1_velocity.hip", "m1_velocity_freq.hip"]
 ARCH = "gfx950"
 # per-source flags: the 3-D step kernel is scheduled for instruction-level parallelism (its two
 # waves per SIMD leave latency to hide; measured 1 % faster in FP64 and MIXED on MI355X)

@@ -119,9 +119,8 @@ struct WaveDiag {
   int nun = 0, nnp = 0;
 };
 template <typename S, int ND>
-__device__ __forceinline__ void wave_diag(double c, double E1, const double F1[3], unsigned long long upd,
-                                          WaveDiag& wd) {
-  wd.esum += E1;
+__device__ __forceinline__ void wave_diag_count(double c, double E1, const double F1[3], unsigned long long upd,
+                                                WaveDiag& wd) {
   double Es = E1, F2 = 0.0;
   for (int k = 0; k < ND; ++k) F2 += F1[k] * F1[k];
   // |E| below 2^-400: the squares could underflow; f and the counts are those of the state
@@ -143,6 +142,12 @@ __device__ __forceinline__ void wave_diag(double c, double E1, const double F1[3
   // |F^| > lim: every state with E < 0 counts, else compare the squares
   wd.nun += __builtin_popcountll(__builtin_amdgcn_ballot_w64(lim < 0.0 || F2 > lim * lim) & upd);
   wd.nnp += __builtin_popcountll(__builtin_amdgcn_ballot_w64(!(E1 > 0.0)) & upd);
+}
+template <typename S, int ND>
+__device__ __forceinline__ void wave_diag(double c, double E1, const double F1[3], unsigned long long upd,
+                                          WaveDiag& wd) {
+  wd.esum += E1;
+  wave_diag_count<S, ND>(c, E1, F1, upd, wd);
 }
 
 // The block's partials of the diagnostics from its waves' (nw <= 16), each zone's volume V the

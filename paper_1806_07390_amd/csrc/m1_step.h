@@ -46,4 +46,9 @@ int launch_c3(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, hipSt
 template <typename S>
 int launch_c3_vel(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, const VelArgs<S>& va, hipStream_t st);
 
+// Step 2 of the velocity step and the interaction update in double with whole zones per wave
+// (m1_velocity_freq.hip; at most 64 groups), in place on the output; nblocks: the partials written.
+int launch_vel_freq_wave(const fornax_m1_ctx* ctx, const StepArgs<double>& b, const VelArgs<double>& va, int* nblocks,
+                         int want, hipStream_t st);
+
 }  // namespace fm1

@@ -15,7 +15,8 @@
 //                   Step 1 runs on that kernel instead (m1_step_3d.hip: the transport with
 //                   the advective fluxes), and the zone-local velocity terms of the flux rows
 //                   move to k_vel_freq, which reads F^n for them;
-//   k_vel_freq      whole zones per block (BLOCK / G zones of G groups, lanes = groups): Step 2
+//   k_vel_freq      (in double with at most 64 groups k_vel_freq_wave, m1_velocity_freq.hip)
+//                   whole zones per block (BLOCK / G zones of G groups, lanes = groups): Step 2
 //                   on U^(1) (the compression work, and the upwind intergroup fluxes of the
 //                   energy and of the flux components from the minmod-reconstructed spectral
 //                   densities, neighbours through LDS), then the interaction update, dE_matter
@@ -527,13 +528,27 @@ int launch_vel_nd(fornax_m1_ctx* ctx, const Geo<R>& geo, StepArgs<S>& a, const V
   const bool want = diag && (diag->energy_total || diag->max_f || diag->n_unrealizable || diag->n_nonpositive);
   b.dEm = diag ? diag->dE_matter : nullptr;
   const int64_t need = (a.nzones + a.zones_per_block - 1) / a.zones_per_block;
-  const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(need, std::min<int64_t>(ctx->nb_partials, 65536)));
+  int nb = (int)std::max<int64_t>(1, std::min<int64_t>(need, std::min<int64_t>(ctx->nb_partials, 65536)));
   b.p_energy = ctx->p_energy;
   b.p_maxf2 = ctx->p_maxf2;
   b.p_nun = ctx->p_nun;
   b.p_nnp = ctx->p_nnp;
-  hipLaunchKernelGGL((k_vel_freq<S, R, SPH, ND>), dim3(nb), dim3(BLOCK), 0, st, b, geo, vf, want ? 1 : 0);
-  if (hipGetLastError() != hipSuccess) return FORNAX_EDEVICE;
+  // In double with at most 64 groups whole zones per wave: faster than whole zones per block at
+  // every size measured, also where 64 / G leaves lanes idle (96 x 80 x 64 zones, the whole step:
+  // 12 % at 16 groups, 11 % at 22, 5 % at 33; 256 x 256 zones 14 % at 12 groups).  Float keeps the
+  // block kernel and its results bit for bit (see choose_c3_tile).
+  bool done = false;
+  if constexpr (std::is_same<R, double>::value) {
+    if (a.G <= 64) {
+      const int rc = launch_vel_freq_wave(ctx, b, vf, &nb, want ? 1 : 0, st);
+      if (rc != FORNAX_OK) return rc;
+      done = true;
+    }
+  }
+  if (!done) {
+    hipLaunchKernelGGL((k_vel_freq<S, R, SPH, ND>), dim3(nb), dim3(BLOCK), 0, st, b, geo, vf, want ? 1 : 0);
+    if (hipGetLastError() != hipSuccess) return FORNAX_EDEVICE;
+  }
   if (want) return fm1_launch_finalize(ctx->p_energy, ctx->p_maxf2, ctx->p_nun, ctx->p_nnp, nb, diag, st);
   return FORNAX_OK;
 }
