@@ -55,6 +55,24 @@ __device__ __forceinline__ double lane_pair_sum(double v) {
   return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
 }
 
+template <int CTRL>
+__device__ __forceinline__ double row_dpp(double v) {
+  return __builtin_amdgcn_update_dpp(0.0, v, CTRL, 0xf, 0xf, true);
+}
+
+// sum of v over the 2^lg lanes of a zone, in every lane: butterfly order; inside a 16-lane row
+// by lane permutations of the VALU (neighbour pairs, pairs of pairs, mirrored halves and rows:
+// the lanes of a pair or a half hold equal sums by then)
+__device__ __forceinline__ double zone_sum(double v, int lg) {
+  if (lg >= 1) v += row_dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+  if (lg >= 2) v += row_dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  if (lg >= 3) v += row_dpp<0x141>(v);   // row_half_mirror
+  if (lg >= 4) v += row_dpp<0x140>(v);   // row_mirror
+  if (lg >= 5) v += __shfl_xor(v, 16);
+  if (lg >= 6) v += __shfl_xor(v, 32);
+  return v;
+}
+
 // the advective flux v U of the upwind face state added to a face flux (the left state where
 // v >= 0)
 template <typename R>

@@ -29,6 +29,7 @@
 
 #include "m1_device.h"
 #include "m1_internal.h"
+#include "m1_lane.h"
 #include "m1_step.h"
 
 namespace fm1 {
@@ -313,7 +314,8 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
   const bool do_yf = (DIM == 3) && recon && cy <= TYB - 2 && gy + 1 <= n1 && cx >= 1 && cx <= TXB - 2 && gx < n0;
 
   const bool want_diag = a.p_energy != nullptr;
-  ZoneDiag zd;
+  WaveDiag wd;
+  const unsigned long long updm = __builtin_amdgcn_ballot_w64(upd);
   const R c = R(a.c);
   const R dtR = R(a.dt);
   // extended indices of the column for table lookups (clamped: columns beyond the second
@@ -455,6 +457,10 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
   const double cdt = a.c * a.dt;
   R q0[V][4], q1[V][4];
   R hiM[V][4], fPrev[V][4];
+  // double: |F^|^2 and cE of hiM and of the in-plane upper states, for the closure (where the
+  // registers are there: not on spherical grids, in 3-D or with two groups per lane)
+  constexpr bool DX = sizeof(R) == 8 && !SPH && DIM < 3 && V == 1;
+  FaceAux<R> xM[V] = {};
   R ks0[V], ks1[V];
   double ck0[V], cks0[V], ck1[V], cks1[V];
   for (int u = 0; u < V; ++u) {
@@ -496,7 +502,8 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
       for (int u = 0; u < V; ++u) {
         R lo[4], hiP[4];
         reconstruct<R, SPH, DIM, LIM>(a, geo, MD, ef - 1, qa[u], qb[u], q0[u], ih0, ih1, o0, o1, lo, hiP);
-        reconstruct<R, SPH, DIM, LIM>(a, geo, MD, ef, qb[u], q0[u], q1[u], ih1, ih2, o1, o2, lo, hiM[u]);
+        reconstruct<R, SPH, DIM, LIM>(a, geo, MD, ef, qb[u], q0[u], q1[u], ih1, ih2, o1, o2, lo, hiM[u], nullptr,
+                                      nullptr, DX ? &xM[u] : nullptr);
         if (o1) hll<R, SPH, DIM, (LIM < 0)>(a, MD, hiP, lo, h1, ih1, epsilon_of(ka[u] + sa[u], ks0[u], dlL, dlR), fPrev[u]);
       }
     } else {
@@ -515,6 +522,11 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
 
   const int prow_own = (DIM == 3) ? cy + 1 : 0;
   const R idx0 = geo.idx[0], idx1 = geo.idx[1], idxM = geo.idx[(DIM >= 2) ? MD : 0];
+  // eq:epsilon on the d-faces: proper widths on spherical grids, else the uniform width
+  auto eps_face = [&](int d, R ksL, R ksR, R dlL, R dlR) -> R {
+    if constexpr (SPH) return epsilon_of(ksL, ksR, dlL, dlR);
+    else return epsilon_uniform(ksL, ksR, R(0.5) * geo.dx[d]);
+  };
   int dz_zone = -1;
   for (int m = mbeg; m < mend; ++m) {
     // ---- consume the values loaded one plane ago ----
@@ -554,6 +566,7 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
     // ---- (c) in-plane reconstruction (lower states to LDS), march face m + 1/2 ----
     const int eym = ey_of(m);
     R hiX[V][4], hiY[V][4];
+    FaceAux<R> xX[V], xY[V];
     for (int u = 0; u < V; ++u)
       for (int k = 0; k < 4; ++k) hiX[u][k] = hiY[u][k] = R(0);
     if (recon) {
@@ -567,7 +580,8 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
           qm[v] = (v < NC) ? PV[pvi(v, prow_own, cx) + u] : R(0);
           qp[v] = (v < NC) ? PV[pvi(v, prow_own, cx + 2) + u] : R(0);
         }
-        reconstruct<R, SPH, DIM, LIM>(a, geo, 0, ex, qm, q0[u], qp, hlo, hhi, olo, ohi, lo, hiX[u]);
+        reconstruct<R, SPH, DIM, LIM>(a, geo, 0, ex, qm, q0[u], qp, hlo, hhi, olo, ohi, lo, hiX[u], nullptr,
+                                      nullptr, DX ? &xX[u] : nullptr);
         for (int v = 0; v < NC; ++v) LX[cidx(v, col) + u] = lo[v];
       }
       if constexpr (DIM == 3) {
@@ -580,7 +594,8 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
             qm[v] = (v < NC) ? PV[pvi(v, prow_own - 1, cx + 1) + u] : R(0);
             qp[v] = (v < NC) ? PV[pvi(v, prow_own + 1, cx + 1) + u] : R(0);
           }
-          reconstruct<R, SPH, DIM, LIM>(a, geo, 1, eyc, qm, q0[u], qp, hlo, hhi, ylo, yhi, lo, hiY[u]);
+          reconstruct<R, SPH, DIM, LIM>(a, geo, 1, eyc, qm, q0[u], qp, hlo, hhi, ylo, yhi, lo, hiY[u], nullptr,
+                                        nullptr, DX ? &xY[u] : nullptr);
           for (int v = 0; v < NC; ++v) LY[cidx(v, col) + u] = lo[v];
         }
       }
@@ -602,8 +617,12 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
         const R dlR = proper_width<R, SPH>(geo, MD, ex, (DIM == 3) ? eyc : ef);
         for (int u = 0; u < V; ++u) {
           R nLo[4];
-          reconstruct<R, SPH, DIM, LIM>(a, geo, MD, ef, q0[u], q1[u], q2[u], ih1, ih2, o1, o2, nLo, nHi[u]);
-          if (o1) hll<R, SPH, DIM, (LIM < 0)>(a, MD, hiM[u], nLo, h1, ih1, epsilon_of(ks0[u], ks1[u], dlL, dlR), fNext[u]);
+          FaceAux<R> xLo, xHi;
+          reconstruct<R, SPH, DIM, LIM>(a, geo, MD, ef, q0[u], q1[u], q2[u], ih1, ih2, o1, o2, nLo, nHi[u], nullptr,
+                                        DX ? &xLo : nullptr, DX ? &xHi : nullptr);
+          if (o1) hll<R, SPH, DIM, (LIM < 0)>(a, MD, hiM[u], nLo, h1, ih1, eps_face(MD, ks0[u], ks1[u], dlL, dlR), fNext[u],
+                                                    DX ? &xM[u] : nullptr, DX ? &xLo : nullptr);
+          if constexpr (DX) xM[u] = xHi;
         }
       }
     }
@@ -623,7 +642,7 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
         R qR[4] = {R(0), R(0), R(0), R(0)};
         for (int v = 0; v < NC; ++v) qR[v] = LX[cidx(v, col + 1) + u];
         const R ksR = PV[pvi(NC, prow_own, cx + 2) + u];
-        if (open) hll<R, SPH, DIM, (LIM < 0)>(a, 0, hiX[u], qR, hf, ihf, epsilon_of(ks0[u], ksR, dlL, dlR), fxR[u]);
+        if (open) hll<R, SPH, DIM, (LIM < 0)>(a, 0, hiX[u], qR, hf, ihf, eps_face(0, ks0[u], ksR, dlL, dlR), fxR[u], DX ? &xX[u] : nullptr);
         for (int v = 0; v < NC; ++v) FX[cidx(v, col) + u] = fxR[u][v];
       }
     }
@@ -639,7 +658,7 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
           R qR[4] = {R(0), R(0), R(0), R(0)};
           for (int v = 0; v < NC; ++v) qR[v] = LY[cidx(v, col + TXB) + u];
           const R ksR = PV[pvi(NC, prow_own + 1, cx + 1) + u];
-          if (open) hll<R, SPH, DIM, (LIM < 0)>(a, 1, hiY[u], qR, hf, ihf, epsilon_of(ks0[u], ksR, dlL, dlR), fyR[u]);
+          if (open) hll<R, SPH, DIM, (LIM < 0)>(a, 1, hiY[u], qR, hf, ihf, eps_face(1, ks0[u], ksR, dlL, dlR), fyR[u], DX ? &xY[u] : nullptr);
           for (int v = 0; v < NC; ++v) FY[cidx(v, col) + u] = fyR[u][v];
         }
       }
@@ -647,6 +666,8 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
     unit_sync<ROW>();
     // ---- (e) update ----
     dz_zone = -1;
+    S Eo[V], Fo[3][V];
+    for (int u = 0; u < V; ++u) Eo[u] = Fo[0][u] = Fo[1][u] = Fo[2][u] = S(0);
     if (upd) {
       R wxl = R(1), wxh = R(1), iWx = idx0;
       if constexpr (SPH) {
@@ -668,7 +689,6 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
       }
       const int zi = gx, zj = (DIM == 2) ? m : gy, zk = (DIM == 3) ? m : 0;
       const int zone = (zk * n1 + zj) * n0 + zi;
-      S Eo[V], Fo[3][V];
       double dzs = 0.0;
       for (int u = 0; u < V; ++u) {
         R acc[4] = {R(0), R(0), R(0), R(0)};
@@ -696,7 +716,7 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
         S F1[3];
         double dz = 0.0;
         if (a.src) {
-          dz = source_zone<S, R, SPH, DIM>(a, geo, zi, zj, Um, ck0[u], cks0[u], jB[u], want_diag, Vm, zd, Eo[u], F1);
+          dz = source_update<S, R, DIM>(Um, ck0[u], cks0[u], jB[u], Eo[u], F1);
         } else {
           Eo[u] = S(Um[0]);
           for (int cc = 0; cc < DIM; ++cc) F1[cc] = S(Um[1 + cc]);
@@ -711,9 +731,28 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
       if (!ROW && a.dEm) dz_zone = zone;
       if (ROW && a.dEm) {
         // sum over the groups of this column (consecutive lanes), one partial per wave
+        // (a compile-time count of at most 16 lanes: by the VALU's lane permutations)
         double p = dzs;
-        for (int off = 1; off < LPC; off <<= 1) p += __shfl_xor(p, off);
+        if constexpr (GBC > 0 && GBC / V <= 16) p = zone_sum(p, __builtin_ctz(GBC / V));
+        else
+          for (int off = 1; off < LPC; off <<= 1) p += __shfl_xor(p, off);
         if (gl == 0) DZ[((size_t)(m - mbeg) * tl.NW + wv) * TXB + cx] = p;
+      }
+    }
+    // ---- diagnostics (all lanes of the wave; those of columns not updated hold zeros) ----
+    if (want_diag) {
+      for (int u = 0; u < V; ++u) {
+        double Fd[3] = {0.0, 0.0, 0.0};
+        for (int cc = 0; cc < DIM; ++cc) Fd[cc] = (double)Fo[cc][u];
+        if constexpr (SPH) {
+          const double hd = (double)gld(geo.hr, ex);
+          const double ih = rcp_(hd);
+          Fd[0] *= ih;
+          Fd[1] *= ih;
+          Fd[2] *= rcp_(hd * (double)gld(geo.hs, (DIM == 3) ? eyc : (DIM == 2) ? m + NG : NG));
+        }
+        wd.esum += Vm * (double)Eo[u];
+        wave_diag_count<S, DIM>(a.c, (double)Eo[u], Fd, updm, wd);
       }
     }
     // ---- advance the window ----
@@ -755,13 +794,10 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
   }
   if (!want_diag) return;
   // ---- block partials of the diagnostics: wave reduction, then across waves ----
-  double e = zd.energy, mf = zd.maxf2();
-  int un = zd.nun, p = zd.nnp;
+  double e = wd.esum, mf = wd.fnum / wd.fden;
   for (int off = 32; off > 0; off >>= 1) {
     e += __shfl_xor(e, off);
     mf = fmax(mf, __shfl_xor(mf, off));
-    un += __shfl_xor(un, off);
-    p += __shfl_xor(p, off);
   }
   __shared__ double we[16], wm[16];
   __shared__ int wu[16], wp[16];
@@ -770,8 +806,8 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
   if (lane == 0) {
     we[wave] = e;
     wm[wave] = mf;
-    wu[wave] = un;
-    wp[wave] = p;
+    wu[wave] = wd.nun;
+    wp[wave] = wd.nnp;
   }
   __syncthreads();
   if (threadIdx.x == 0) {

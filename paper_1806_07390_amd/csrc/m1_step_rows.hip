@@ -28,6 +28,7 @@
 
 #include "m1_device.h"
 #include "m1_internal.h"
+#include "m1_lane.h"
 #include "m1_step.h"
 
 namespace fm1 {
@@ -188,11 +189,13 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
   const bool upd = c >= 1 && c <= RTX - 2 && gx < n0;
   const bool do_xf = c <= RTX - 2 && gx + 1 <= n0;
   const bool want_diag = a.p_energy != nullptr;
-  ZoneDiag zd;
+  WaveDiag wd;
+  const unsigned long long updm = __builtin_amdgcn_ballot_w64(upd);
   const double cdt = a.c * a.dt;
   const R dtR = R(a.dt);
   const R idx0 = geo.idx[0], idx1 = geo.idx[1];
-  const R dx0 = geo.dx[0], dx1 = geo.dx[1];
+  const R hdx0 = R(0.5) * geo.dx[0], hdx1 = R(0.5) * geo.dx[1];
+  constexpr bool DX = sizeof(R) == 8;   // double: |F^|^2 and cE of the face states for the closure
   const R hone[3] = {R(1), R(1), R(1)};
   const double Vz = want_diag ? geo.Wd[0][NG] * geo.Wd[1][NG] * geo.Wd[2][NG] : 0.0;   // uniform zones
 
@@ -390,12 +393,14 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
   lds_read3<L::arr_bytes(3), L::arr_bytes(4), L::arr_bytes(5)>(bco, bco, bco, k0v);
   R ks0 = R(k0v[0]) + R(k0v[1]);
   double ck0 = cdt * (double)k0v[0], cks0 = cdt * ((double)k0v[0] + (double)k0v[1]);
+  FaceAux<R> xM{};
   for (int k = 0; k < 4; ++k) hiM[k] = fPrev[k] = R(0);
   {
     R lo[4], hiP[4];
     reconstruct<R, false, 2, LIM>(a, geo, 1, mbeg - 1 + NG, qa, qb, q0, hone, hone, true, true, lo, hiP);
-    reconstruct<R, false, 2, LIM>(a, geo, 1, mbeg + NG, qb, q0, q1, hone, hone, true, true, lo, hiM);
-    hll<R, false, 2>(a, 1, hiP, lo, hone, hone, epsilon_of(ksb, ks0, dx1, dx1), fPrev);
+    reconstruct<R, false, 2, LIM>(a, geo, 1, mbeg + NG, qb, q0, q1, hone, hone, true, true, lo, hiM, nullptr, nullptr,
+                                  DX ? &xM : nullptr);
+    hll<R, false, 2>(a, 1, hiP, lo, hone, hone, epsilon_uniform(ksb, ks0, hdx1), fPrev);
   }
 
   // outputs of the previous plane, stored at the top of the next one (behind the loads of
@@ -439,18 +444,20 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
       lds_read8<B0, B0 + L::arr_bytes(1), B0 + L::arr_bytes(2), B0, B0 + L::arr_bytes(1), B0 + L::arr_bytes(2),
                 B0 + L::arr_bytes(3), B0 + L::arr_bytes(4)>(bcm, bcp, bcr, xv);
       R hiX[4] = {R(0), R(0), R(0), R(0)}, lo[4] = {R(0), R(0), R(0), R(0)};
+      FaceAux<R> xX{};
       if (recon) {
         R qm[4] = {R(xv[0]), R(xv[1]), R(xv[2]), R(0)}, qp[4] = {R(xv[3]), R(xv[4]), R(xv[5]), R(0)};
         fix_state(qm, xf_m, 0);
         fix_state(qp, xf_p, 0);
-        reconstruct<R, false, 2, LIM>(a, geo, 0, gx + NG, qm, q0, qp, hone, hone, true, true, lo, hiX);
+        reconstruct<R, false, 2, LIM>(a, geo, 0, gx + NG, qm, q0, qp, hone, hone, true, true, lo, hiX, nullptr,
+                                      nullptr, DX ? &xX : nullptr);
       }
       R qR[4] = {R(0), R(0), R(0), R(0)};
       for (int v = 0; v < RNC; ++v) qR[v] = lane_fetch(up_addr, lo[v]);
       R fx[4] = {R(0), R(0), R(0), R(0)};
       if (do_xf) {
         const R ksR = R(xv[6]) + R(xv[7]);
-        hll<R, false, 2>(a, 0, hiX, qR, hone, hone, epsilon_of(ks0, ksR, dx0, dx0), fx);
+        hll<R, false, 2>(a, 0, hiX, qR, hone, hone, epsilon_uniform(ks0, ksR, hdx0), fx, DX ? &xX : nullptr);
       }
       for (int v = 0; v < RNC; ++v) acc[v] += (fx[v] - lane_fetch(dn_addr, fx[v])) * idx0;
     }
@@ -468,8 +475,12 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
     R fNext[4] = {R(0), R(0), R(0), R(0)}, nHi[4] = {R(0), R(0), R(0), R(0)};
     if (upd) {
       R nLo[4];
-      reconstruct<R, false, 2, LIM>(a, geo, 1, m + 1 + NG, q0, q1, q2, hone, hone, true, true, nLo, nHi);
-      hll<R, false, 2>(a, 1, hiM, nLo, hone, hone, epsilon_of(ks0, ks1, dx1, dx1), fNext);
+      FaceAux<R> xLo, xHi;
+      reconstruct<R, false, 2, LIM>(a, geo, 1, m + 1 + NG, q0, q1, q2, hone, hone, true, true, nLo, nHi, nullptr,
+                                    DX ? &xLo : nullptr, DX ? &xHi : nullptr);
+      hll<R, false, 2>(a, 1, hiM, nLo, hone, hone, epsilon_uniform(ks0, ks1, hdx1), fNext, DX ? &xM : nullptr,
+                       DX ? &xLo : nullptr);
+      if constexpr (DX) xM = xHi;
     }
     // update of the own zone (stored at the top of the next plane)
     S Eo = S(0), F1[3] = {S(0), S(0), S(0)};
@@ -477,13 +488,16 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
       for (int v = 0; v < RNC; ++v) acc[v] += (fNext[v] - fPrev[v]) * idx1;
       R Um[4];
       for (int k = 0; k < 4; ++k) Um[k] = (k < RNC) ? q0[k] - dtR * acc[k] : R(0);
-      const double dz = source_zone<S, R, false, 2>(a, geo, gx, m, Um, ck0, cks0, jB, want_diag, Vz, zd, Eo, F1);
+      const double dz = source_update<S, R, 2>(Um, ck0, cks0, jB, Eo, F1);
       if (a.dEm) {
-        double p = dz;
-        p += __shfl_xor(p, 1);
-        p += __shfl_xor(p, 2);
+        const double p = zone_sum(dz, 2);
         if ((lane & 3) == 0) DZ[m & 1][w][c] = p;
       }
+    }
+    // (all lanes of the wave; those of columns not updated hold zeros)
+    if (want_diag) {
+      const double Fd[3] = {(double)F1[0], (double)F1[1], 0.0};
+      wave_diag<S, 2>(a.c, (double)Eo, Fd, updm, wd);
     }
     off_o = upd ? (uint32_t)((((size_t)m * n0 + gx) * RG + g) * sizeof(S)) : 0x7ffffff0u;
     Eo_o = Eo;
@@ -516,35 +530,7 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
 
   if (!want_diag) return;
   // ---- block partials of the diagnostics ----
-  double e = zd.energy, mf = zd.maxf2();
-  int un = zd.nun, pnp = zd.nnp;
-  for (int off = 32; off > 0; off >>= 1) {
-    e += __shfl_xor(e, off);
-    mf = fmax(mf, __shfl_xor(mf, off));
-    un += __shfl_xor(un, off);
-    pnp += __shfl_xor(pnp, off);
-  }
-  if (lane == 0) {
-    we[w] = e;
-    wm[w] = mf;
-    wu[w] = un;
-    wp[w] = pnp;
-  }
-  __syncthreads();
-  if (t == 0) {
-    double se = 0.0, sm = 0.0;
-    int su = 0, sp = 0;
-    for (int k = 0; k < NW; ++k) {
-      se += we[k];
-      sm = fmax(sm, wm[k]);
-      su += wu[k];
-      sp += wp[k];
-    }
-    a.p_energy[blockIdx.x] = se;
-    a.p_maxf2[blockIdx.x] = sm;
-    a.p_nun[blockIdx.x] = su;
-    a.p_nnp[blockIdx.x] = sp;
-  }
+  wave_diag_store(wd, upd, Vz, w, lane, NW, we, wm, wu, wp, a.p_energy, a.p_maxf2, a.p_nun, a.p_nnp);
 }
 
 #undef FM1_LDSP
