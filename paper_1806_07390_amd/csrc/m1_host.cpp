@@ -444,6 +444,9 @@ int fornax_m1_create(const fornax_m1_desc* desc, fornax_m1_ctx** out) {
       if (s > worst) worst = s;
     }
   ctx->max_dt1 = 1.0 / worst;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) cus = 0;
+  ctx->cus = cus;
   // tiling of the step kernel (FORNAX_M1_TILE="TXB,TYB,TM[,GB]" overrides the default choice)
   if (prepare_step_kernels() != FORNAX_OK) {
     (void)hipFree(ctx->geo_mem);
@@ -459,9 +462,9 @@ int fornax_m1_create(const fornax_m1_desc* desc, fornax_m1_ctx** out) {
                    desc->ngroups % 2 == 0 && !(pe && pe[0] == '0'))
                       ? 2
                       : 1;
-    ctx->tile = choose_tile(*desc, V);
-    if (ctx->tile.nblocks <= 0) ctx->tile = choose_tile(*desc, 1);
-    ctx->tile_v1 = (ctx->tile.V == 1) ? ctx->tile : choose_tile(*desc, 1);
+    ctx->tile = choose_tile(*desc, V, cus);
+    if (ctx->tile.nblocks <= 0) ctx->tile = choose_tile(*desc, 1, cus);
+    ctx->tile_v1 = (ctx->tile.V == 1) ? ctx->tile : choose_tile(*desc, 1, cus);
   }
   if (const char* env = std::getenv("FORNAX_M1_TILE")) {
     // "TXB,TYB,TM,GB[,NW[,V]]" (TXB, TYB ignored for 1-D/2-D wave rows, where TXB = 64 V/GB)
@@ -479,9 +482,6 @@ int fornax_m1_create(const fornax_m1_desc* desc, fornax_m1_ctx** out) {
   }
   // the whole-zone kernel where the grid qualifies (FORNAX_M1_ROWS="0" disables it,
   // "NWX,TM" picks its tiling)
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess) cus = 0;
-  ctx->cus = cus;
   ctx->rows = choose_rows_tile(*desc, cus);
   if (const char* env = std::getenv("FORNAX_M1_ROWS")) {
     int nwx = 0, tm = 0;

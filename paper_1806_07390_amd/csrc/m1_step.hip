@@ -25,6 +25,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "m1_device.h"
@@ -900,11 +901,49 @@ Tile make_tile(const fornax_m1_desc& D, int TXB, int TYB, int TM, int GB, int NW
 //  * 1-D / 2-D wave rows: with V = 2 (G even) each lane takes a pair of groups and GB = the
 //    largest power of two up to 8 dividing G, so that a wave row of 16 columns reads runs of
 //    8 groups; with V = 1, GB up to 4.  All G / GB group subsets of a tile share a block when
-//    they fit in 8 waves.  Planes per block are halved from 32 until the grid has at least
-//    1024 (FP64) or 2048 (MIXED) blocks, TM >= 4.
+//    they fit in 8 waves.  Planes per block (2-D): see rows_by_rounds.
 //  * 3-D: a near-square tile of 128-512 threads; with many groups per zone, groups are split
 //    across blocks so that the zone tile stays large enough to amortise its halo.
-Tile choose_tile(const fornax_m1_desc& D, int V) {
+template <typename S, bool SPH>
+static const void* row_kernel(const Tile& tl, bool mm) {
+  constexpr int MM = FORNAX_LIMITER_MINMOD;
+  if (tl.GB == 4) return mm ? (const void*)&k_step_tiled<S, S, 2, SPH, true, 4, 1, MM> : (const void*)&k_step_tiled<S, S, 2, SPH, true, 4, 1, -1>;
+  return mm ? (const void*)&k_step_tiled<S, S, 2, SPH, true, 0, 1, MM> : (const void*)&k_step_tiled<S, S, 2, SPH, true, 0, 1, -1>;
+}
+
+// 2-D wave rows with one group per lane: a block walks its TM planes (and about three planes'
+// worth of start-up) one after the other, so the kernel takes about the number of rounds of block
+// slots times TM + 3; the TM with the least such cost, the slots from the kernel's occupancy.
+// Against the largest power of two with 1024 (double) or 2048 (float) blocks: 512 x 512 x 16
+// double PPM RK2 297 -> 278 us (16 -> 26 planes), MIXED 79.4 -> 77.9 (8 -> 16), 301 x 187 x 9 double
+// MC 40 -> 33 (4 -> 6), 384 x 384 x 12 double 58 -> 48 (4 -> 11), 400 x 300 x 8 double 37 -> 32
+// (4 -> 6); small grids keep 4 planes.
+static Tile rows_by_rounds(const fornax_m1_desc& D, int GB, int NW, int cus) {
+  const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
+  const bool mm = D.limiter == FORNAX_LIMITER_MINMOD && D.wavespeed == FORNAX_WAVESPEED_LIGHT;
+  Tile best{};
+  double best_cost = 0.0;
+  for (int TM = 4; TM <= 64; ++TM) {
+    const Tile t = make_tile(D, 0, 1, TM, GB, NW, 1);
+    if (t.nblocks <= 0) continue;
+    const void* k = D.precision == FORNAX_FP64 ? (sph ? row_kernel<double, true>(t, mm) : row_kernel<double, false>(t, mm))
+                                               : (sph ? row_kernel<float, true>(t, mm) : row_kernel<float, false>(t, mm));
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, t.nthreads, t.lds) != hipSuccess || per_cu < 1) {
+      (void)hipGetLastError();
+      per_cu = std::max(1, 8 / NW);
+    }
+    const int64_t slots = (int64_t)per_cu * (cus > 0 ? cus : 256);
+    const double cost = (double)((t.nblocks + slots - 1) / slots) * (TM + 3);
+    if (best.nblocks <= 0 || cost <= best_cost) {
+      best = t;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+Tile choose_tile(const fornax_m1_desc& D, int V, int cus) {
   const int G = D.ngroups;
   if (V == 2 && G % 2 != 0) return Tile{};
   if (D.ndim < 3) {
@@ -912,13 +951,8 @@ Tile choose_tile(const fornax_m1_desc& D, int V) {
     while (GB < 4 * V && G % (2 * GB) == 0) GB *= 2;
     int NW = std::min(8, G / GB);
     while ((G / GB) % NW != 0) --NW;
-    const int want = (D.precision == FORNAX_FP64) ? 1024 : 2048;
-    Tile t{};
-    for (int TM = 32; TM >= 4; TM /= 2) {
-      t = make_tile(D, 0, 1, TM, GB, NW, V);
-      if (t.nblocks >= want || D.ndim == 1) break;
-    }
-    return t;
+    if (D.ndim == 1) return make_tile(D, 0, 1, 1, GB, NW, V);
+    return rows_by_rounds(D, GB, NW, cus);
   }
   // measured on gfx950 (192^3 x 12 and 256 x 64 x 128 x 20): Cartesian FP64 8 x 8 columns of
   // up to 4 groups, 16 planes; Cartesian FP32 pairs of groups per lane, 16 x 16 columns of 2
