@@ -227,6 +227,7 @@ k_adjoint(AdjArgs<S> a, Geo<R> geo, AdjTile tl) {
   auto plane_step = [&](auto rt_c, const int m) {
     constexpr int RT = decltype(rt_c)::value;
     auto sl = [](int i) { return (i + RT) & 3; };
+    if constexpr (DIM >= 2) prio_by_progress(m - mbeg, (tl.TM + 3) / 4);
     const bool rowin = (DIM < 2) || (m >= 0 && m < nM);
     // ---- march: load plane m+3, face m+2 ----
     if constexpr (DIM >= 2) {

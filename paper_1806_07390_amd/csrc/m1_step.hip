@@ -529,7 +529,9 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
     else return epsilon_uniform(ksL, ksR, R(0.5) * geo.dx[d]);
   };
   int dz_zone = -1;
+  const int pq = (tl.TM + 3) / 4;
   for (int m = mbeg; m < mend; ++m) {
+    if constexpr (ROW && DIM == 2) prio_by_progress(m - mbeg, pq);
     // ---- consume the values loaded one plane ago ----
     R q2[V][4];
     fix_all(Pr, Ppm, q2);   // plane m + 2

@@ -514,7 +514,9 @@ k_step_rows(StepArgs<S> a, Geo<S> geo, RowsTile tl) {
     ck0 = ck1;
     cks0 = cks1;
   };
+  const int pq = (tl.TM + 3) / 4;
   for (int m = mbeg; m < mend; m += 4) {
+    prio_by_progress(m - mbeg, pq);
     plane(m, std::integral_constant<int, 0>{});
     if (m + 1 < mend) plane(m + 1, std::integral_constant<int, 1>{});
     if (m + 2 < mend) plane(m + 2, std::integral_constant<int, 2>{});
