@@ -136,7 +136,9 @@ struct WaveDiag {
   double esum = 0.0, fnum = 0.0, fden = 1.0;
   int nun = 0, nnp = 0;
 };
-template <typename S, int ND>
+// SEL: by selects in every wave instead (the 2-D tiles, whose planes are short chains of
+// latencies: 512 x 512 x 16 0.7 % faster than with the branch; the 3-D kernel the other way round).
+template <typename S, int ND, bool SEL = false>
 __device__ __forceinline__ void wave_diag_count(double c, double E1, const double F1[3], unsigned long long upd,
                                                 WaveDiag& wd) {
   double Es = E1, F2 = 0.0;
@@ -151,7 +153,7 @@ __device__ __forceinline__ void wave_diag_count(double c, double E1, const doubl
   }
   const double cE = c * Es, cE2 = cE * cE;
   const bool up = Es > 0.0 && F2 * wd.fden > wd.fnum * cE2;
-  if (__builtin_amdgcn_ballot_w64(up)) {
+  if (SEL || __builtin_amdgcn_ballot_w64(up)) {
     wd.fnum = up ? F2 : wd.fnum;
     wd.fden = up ? cE2 : wd.fden;
   }

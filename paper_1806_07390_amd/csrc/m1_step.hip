@@ -529,6 +529,11 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
     else return epsilon_uniform(ksL, ksR, R(0.5) * geo.dx[d]);
   };
   int dz_zone = -1;
+  // second Runge-Kutta stage, U^n of the plane's zones: loaded ahead of the plane's work (EA), all
+  // components together at the update in the double kernel that is held to a register budget (EB;
+  // 512 x 512 x 16 PPM RK2 262 -> 243 us against a load and a wait per component, 268 ahead), each
+  // at its use in the float one (any other place spills registers: MIXED blobs 67 -> 69 us)
+  constexpr bool EA = !(GBC > 0 && !SPH && V == 1), EB = !EA && sizeof(R) == 8;
   const int pq = (tl.TM + 3) / 4;
   for (int m = mbeg; m < mend; ++m) {
     if constexpr (ROW && DIM == 2) prio_by_progress(m - mbeg, pq);
@@ -559,6 +564,19 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
       Pvol = plane_vol(m + 1);
       load_halo(m + 1);
     }
+    R Ua[V][4];
+    auto load_ua = [&]() {
+      const int zj = (DIM == 2) ? m : zjb, zk = (DIM == 3) ? m : 0;
+      const int zga = ((zk * n1 + zj) * n0 + zib) * a.G + grp0;
+      R r[V];
+      ldv<S, R, V>(a.Ea, zga, r);
+      for (int u = 0; u < V; ++u) Ua[u][0] = r[u];
+      for (int cc = 0; cc < DIM; ++cc) {
+        ldv<S, R, V>(a.Fa[cc], zga, r);
+        for (int u = 0; u < V; ++u) Ua[u][1 + cc] = r[u];
+      }
+    };
+    if (EA && a.Ea) load_ua();
     unit_sync<ROW>();
     // ---- (b) deferred dE_matter of the previous plane (block units: all groups in the block) ----
     if (!ROW && a.dEm && dz_zone >= 0 && gl == 0) {
@@ -693,6 +711,7 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
       const int zi = gx, zj = (DIM == 2) ? m : gy, zk = (DIM == 3) ? m : 0;
       const int zone = (zk * n1 + zj) * n0 + zi;
       double dzs = 0.0;
+      if (EB && a.Ea) load_ua();
       for (int u = 0; u < V; ++u) {
         R acc[4] = {R(0), R(0), R(0), R(0)};
         for (int v = 0; v < NC; ++v) acc[v] += (wxh * fxR[u][v] - wxl * FX[cidx(v, col - 1) + u]) * iWx;
@@ -712,9 +731,13 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
         }
         if (a.Ea) {
           // second Runge-Kutta stage: the average with U^n
-          const int zgu = zone * a.G + grp0 + u;
-          Um[0] = R(0.5) * (R(a.Ea[zgu]) + Um[0]);
-          for (int cc = 0; cc < DIM; ++cc) Um[1 + cc] = R(0.5) * (R(a.Fa[cc][zgu]) + Um[1 + cc]);
+          if constexpr (EA || EB) {
+            for (int cc = 0; cc < NC; ++cc) Um[cc] = R(0.5) * (Ua[u][cc] + Um[cc]);
+          } else {
+            const int zgu = zone * a.G + grp0 + u;
+            Um[0] = R(0.5) * (R(a.Ea[zgu]) + Um[0]);
+            for (int cc = 0; cc < DIM; ++cc) Um[1 + cc] = R(0.5) * (R(a.Fa[cc][zgu]) + Um[1 + cc]);
+          }
         }
         S F1[3];
         double dz = 0.0;
@@ -755,7 +778,7 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
           Fd[2] *= rcp_(hd * (double)gld(geo.hs, (DIM == 3) ? eyc : (DIM == 2) ? m + NG : NG));
         }
         wd.esum += Vm * (double)Eo[u];
-        wave_diag_count<S, DIM>(a.c, (double)Eo[u], Fd, updm, wd);
+        wave_diag_count<S, DIM, true>(a.c, (double)Eo[u], Fd, updm, wd);
       }
     }
     // ---- advance the window ----
