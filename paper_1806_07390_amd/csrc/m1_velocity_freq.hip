@@ -261,6 +261,9 @@ __global__ void __launch_bounds__(BLOCK, SPH && ND == 3 ? 3 : 4)
     // upper edge) and 1 (at its lower edge): energy row, flux rows
     double W[2][9];
     for (int t = 0; t < 9; ++t) {
+      // (the rounded component, not its last product contracted into the difference, whose
+      // rounding would remain in the part that has to be exactly 0)
+      if ((t / 3 < ND && t % 3 < ND) || (SPH && t % 4 == 0)) __asm__("" : "+v"(Vt[t]));
       W[0][t] = neg_part(Vt[t]);
       W[1][t] = Vt[t] - W[0][t];
     }
