@@ -74,10 +74,10 @@ struct ZoneWalk {
   }
 };
 
-// x where the mask is all ones, where it is 0 a value below 2^-1022 (the top half decides): such a
-// slope or flux leaves any state as it is, and no NaN or infinity of another zone passes
-__device__ __forceinline__ double keep_top(double x, unsigned mask) {
-  const unsigned long long m = ((unsigned long long)mask << 32) | 0xffffffffull;
+// x where the mask is all ones, exactly 0 where it is 0: both halves are cleared, so that nothing of
+// another zone's value (its low bits, a NaN or an infinity) passes a closed edge.
+__device__ __forceinline__ double keep_masked(double x, unsigned mask) {
+  const unsigned long long m = ((unsigned long long)mask << 32) | mask;
   return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, x) & m);
 }
 
@@ -293,10 +293,10 @@ __global__ void __launch_bounds__(BLOCK, SPH && ND == 3 ? 3 : 4)
         const double v = val[sd2][r];
         const double am = (v - wave_prev(v)) * idm;
         const double ap = wave_next(am);
-        ed[sd2] = fma(minmod(keep_top(am, interior), ap), sd2 == 0 ? half : -half, v);
+        ed[sd2] = fma(minmod(keep_masked(am, interior), ap), sd2 == 0 ? half : -half, v);
       }
       const double em = wave_prev(ed[0]);
-      const double fl = keep_top(rnlo * (em + ed[1]), lower);
+      const double fl = keep_masked(rnlo * (em + ed[1]), lower);
       q[r] = fma(dt, (wave_next(fl) - fl) - (r == 0 ? vP : 0.0), q[r]);
     }
     // Steps 3 and 4
