@@ -229,8 +229,9 @@ __global__ void __launch_bounds__(BLOCK, SPH && ND == 3 ? 3 : 4)
         Vt[7] *= r20;
       }
     }
-    // f = F^/(cE), |f| <= 1, and the closure's coefficients over E; E <= 0 and |f| > 1 in a
-    // branch that only waves holding one take
+    // f = F^/(cE), |f| <= 1, and the closure's coefficients over E; E <= 0, |f| > 1 and a subnormal
+    // cE, whose reciprocal is infinite (f^2 is then no number), in a branch that only waves holding
+    // one take
     const double E = q[0];
     double cE = c * E;
     const double icE = rcp_(cE);
@@ -239,8 +240,16 @@ __global__ void __launch_bounds__(BLOCK, SPH && ND == 3 ? 3 : 4)
       f[k] = (SPH ? q[1 + k] * ih[k] : q[1 + k]) * icE;
       f2 = fma(f[k], f[k], f2);
     }
-    if (__builtin_amdgcn_ballot_w64(!(E > 0.0) || f2 > 1.0)) {
+    if (__builtin_amdgcn_ballot_w64(!(E > 0.0) || !(f2 <= 1.0))) {
       __asm__ volatile("");
+      // (the same f for a cE of ordinary size; a tiny one from the state scaled by 2^600, exactly)
+      const double up = cE < 0x1p-400 ? 0x1p600 : 1.0;
+      const double iu = rcp_(c * (E * up));
+      f2 = 0.0;
+      for (int k = 0; k < ND; ++k) {
+        f[k] = (SPH ? q[1 + k] * ih[k] : q[1 + k]) * up * iu;
+        f2 = fma(f[k], f[k], f2);
+      }
       const double sc = rcp_(sqrt_(f2));
       const bool pos = E > 0.0, big = f2 > 1.0;
       for (int k = 0; k < ND; ++k) f[k] = pos ? (big ? f[k] * sc : f[k]) : 0.0;

@@ -88,3 +88,29 @@ def test_closed_edges(kind, G, empty, steps):
     assert int(dg["n_nonpositive"].item()) == diag["n_nonpositive"]
     assert int(dg["n_unrealizable"].item()) == diag["n_unrealizable"]
     assert abs(dg["max_f"].item() - diag["max_f"]) <= TOL_FP64 * diag["max_f"]
+
+
+@pytest.mark.parametrize("kind,G", [("cart2d", 2), ("cart2d", 5), ("cart3d", 8), ("cart3d", 9)])
+def test_subnormal_energies(kind, G):
+    """Energies below the smallest normal number (what is left in a zone that empties) stay finite and
+    follow the oracle.  An operation rounds such values by up to 2.5e-324; a few hundred of them per
+    step, each at most doubled by a later one, stay below 1e-320 (the state: 1e-310)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1806_07390_amd import m1
+    w = workload(kind, G, "zones", 11 + G)
+    rng = np.random.default_rng(G)
+    w.E = 1e-310 * rng.random(w.E.shape)
+    w.F = [0.5 * w.c * w.E * rng.uniform(-1, 1, w.E.shape) for _ in range(w.ndim)]
+    vf = wl.face_velocity(w, amp=0.1, seed=G)
+    nu = np.geomspace(0.5, 20.0, G + 1)
+    ctx = m1.Context(m1.Config.from_workload(w, precision=m1.FP64))
+    ctx.set_group_edges(nu)
+    dt = ctx.max_dt(0.3)
+    d = lambda a: to_dev(np.ascontiguousarray(a), torch.float64)
+    E, F = ctx.step_velocity(d(w.E), [d(f) for f in w.F], d(w.kappa), d(w.sigma), d(w.B), [d(x) for x in vf], dt)
+    torch.cuda.synchronize()
+    Er, Fr, _ = orc.run_v(problem_of(w), w.E, w.F, w.kappa, w.sigma, w.B, vf, nu, dt, 1)
+    assert np.isfinite(Er).all() and np.abs(to_host(E) - Er).max() <= 1e-320
+    for a, b in zip(F, Fr):
+        assert np.abs(to_host(a) - b).max() <= 1e-320
