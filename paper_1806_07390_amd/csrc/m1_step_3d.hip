@@ -362,10 +362,8 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   // the divergence and the flux at its lower y face, kappa, sigma, B).  With the LDS arrays
   // double-buffered by plane parity, the one barrier per plane orders every LDS access: a
   // buffer written for plane m was last read for plane m - 2, before the barrier of m - 1.
-  // (in double the state, the x and z part of the divergence, the lower y flux and the geometric
-  // source are kept as one value, U^n - dt (acc - f_y idx1) ..., a third of the registers; in
-  // float they stay apart, which fixes the order of the roundings.)
-  constexpr bool UA = sizeof(R) == 8;
+  // (The state, the x and z part and the lower y flux stay apart: folded into one value, which takes
+  // a third of the registers, equal y fluxes would no longer cancel exactly.)
   // geometric source terms of the covariant flux components (cell-centred h), from the state qz
   auto add_geometric = [&](const R qz[4], R U[4]) {
     if constexpr (SPH) {
@@ -384,27 +382,21 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   };
   R qU[4], accU[4], fyU[4], kU = R(0), sU = R(0), BU = R(0);
   for (int c = 0; c < 4; ++c) qU[c] = accU[c] = fyU[c] = R(0);
-  const R dty = dtR * idx1;
   // the update of plane mu from the kept values and the y flux that the row above computed for it
   // (every lane of the inner rows computes; the lanes that hold a zone of the tile store); bu: the
   // plane's LDS buffer
   auto update = [&](const int mu, const int bu) {
     const int64_t pu = (int64_t)mu * PL;
     R Um[4];
-    if constexpr (UA) {
-      const R wh = SPH ? dtR * (gld(geo.wf[1], ey + 1) * gld(geo.iW[1], ey)) : dty;
-      for (int c = 0; c < 4; ++c) Um[c] = fma(-wh, FY[bu][c][w + 1][lane], qU[c]);
+    R acc[4];
+    if constexpr (SPH) {
+      const R wl = gld(geo.wf[1], ey), wh = gld(geo.wf[1], ey + 1), iW = gld(geo.iW[1], ey);
+      for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (wh * FY[bu][c][w + 1][lane] - wl * fyU[c]) * iW;
     } else {
-      R acc[4];
-      if constexpr (SPH) {
-        const R wl = gld(geo.wf[1], ey), wh = gld(geo.wf[1], ey + 1), iW = gld(geo.iW[1], ey);
-        for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (wh * FY[bu][c][w + 1][lane] - wl * fyU[c]) * iW;
-      } else {
-        for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (FY[bu][c][w + 1][lane] - fyU[c]) * idx1;
-      }
-      for (int c = 0; c < 4; ++c) Um[c] = qU[c] - dtR * acc[c];
-      if constexpr (SPH) add_geometric(qU, Um);
+      for (int c = 0; c < 4; ++c) acc[c] = accU[c] + (FY[bu][c][w + 1][lane] - fyU[c]) * idx1;
     }
+    for (int c = 0; c < 4; ++c) Um[c] = qU[c] - dtR * acc[c];
+    if constexpr (SPH) add_geometric(qU, Um);
     if (RK && a.Ea) {
       // second Runge-Kutta stage: U^- = (U^n + U* + dt L(U*)) / 2
       Um[0] = R(0.5) * (R(ld_off(a.Ea + pu, oz)) + Um[0]);
@@ -635,17 +627,10 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
       }
     }
     // ---- keep what the update of plane m needs; advance the window ----
-    if constexpr (UA) {
-      const R wl = SPH ? gld(geo.wf[1], ey) * gld(geo.iW[1], ey) : idx1;
-      for (int c = 0; c < 4; ++c) qU[c] = q0[c] - dtR * (acc[c] - fy[c] * wl);
-      add_geometric(q0, qU);
-    }
     for (int c = 0; c < 4; ++c) {
-      if constexpr (!UA) {
-        qU[c] = q0[c];
-        accU[c] = acc[c];
-        fyU[c] = fy[c];
-      }
+      qU[c] = q0[c];
+      accU[c] = acc[c];
+      fyU[c] = fy[c];
       q0[c] = q1[c];
       q1[c] = q2[c];
     }
