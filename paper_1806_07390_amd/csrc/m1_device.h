@@ -567,15 +567,16 @@ __device__ __forceinline__ void hll(const StepArgsBase& a, int d, const R qL[4],
   }
   const R half = R(0.5);
   if constexpr (sizeof(R) == 8) {
-    // energy: F^d = F_d / h_d^2, S_R = -S_L = c / h_d (S (E_R - E_L) = (X_R - X_L) / h_d);
+    // energy: F^d = F_d / h_d^2, S_R = -S_L = c / h_d, with c times the difference of the energies
+    // (of nearly equal states it is exact, the difference of their rounded c E is not);
     // covariant flux components: c^2 P^d_k = c T^{dk} h_k / h_d
     const R hc = half * c;
     if constexpr (SPH) {
-      flux[0] = half * ihd * ((qL[1 + d] + qR[1 + d]) * ihd - eps * (aR.X - aL.X));
+      flux[0] = half * ihd * ((qL[1 + d] + qR[1 + d]) * ihd - eps * (c * (qR[0] - qL[0])));
       for (int k = 0; k < ND; ++k)
         flux[1 + k] = hc * ihd * ((PL[k] + PR[k]) * h[k] - (qR[1 + k] - qL[1 + k]));
     } else {
-      flux[0] = half * ((qL[1 + d] + qR[1 + d]) - eps * (aR.X - aL.X));
+      flux[0] = half * ((qL[1 + d] + qR[1 + d]) - eps * (c * (qR[0] - qL[0])));
       for (int k = 0; k < ND; ++k) flux[1 + k] = hc * ((PL[k] + PR[k]) - (qR[1 + k] - qL[1 + k]));
     }
   } else {
