@@ -360,9 +360,9 @@ __global__ void __launch_bounds__(MBLOCK) __attribute__((amdgpu_waves_per_eu(5))
   double kap, B;
   gr.at<1>(&T1, kq, &kap, &B);
   if (on) {
-    a.E[zg] = (S)((Em + cdt * kap * B) * rcp2(1.0 + cdt * kap));
-    const double iden = rcp2(1.0 + cdt * (kap + (double)a.sig[zg]));
-    for (int k = 0; k < a.ndim; ++k) a.F[k][zg] = (S)((double)a.F[k][zg] * iden);
+    a.E[zg] = (S)((Em + cdt * kap * B) / (1.0 + cdt * kap));
+    const double den = 1.0 + cdt * (kap + (double)a.sig[zg]);
+    for (int k = 0; k < a.ndim; ++k) a.F[k][zg] = (S)((double)a.F[k][zg] / den);
   }
   if (g == 0) {
     a.T[z] = T1;
