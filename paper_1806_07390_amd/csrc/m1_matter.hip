@@ -131,15 +131,14 @@ __device__ __forceinline__ double planck_high(double x, double q) {
   return q * fma(x, fma(x, fma(x, a, 3.0 * b), 6.0 * c), 6.0 * d);
 }
 
-// one edge's value at x[0] and, with P = 2, at a nearby x[1] (relatively 1e-7 apart) in the same
-// form: the integral over [x[1], x[0]] by the midpoint rule (its error, the cube of the width, is
-// far below rounding)
+// one edge's value, below the split (low) or above it, at x[0] and, with P = 2, at a nearby x[1]
+// (relatively 1e-7 apart) in the same form: the integral over [x[1], x[0]] by the midpoint rule
+// (its error, the cube of the width, is far below rounding)
 template <int P>
-__device__ __forceinline__ void planck_edge(const double* x, double* v) {
+__device__ __forceinline__ void planck_edge(const double* x, bool low, double* v) {
   const double xc = fmin(x[0], EXP_MAX);
   double q, em;
   exp_neg(xc, q, em);
-  const bool low = x[0] < PLANCK_SPLIT;
   if (low) v[0] = planck_low(xc);
   else v[0] = planck_high(xc, q);
   if constexpr (P == 2) {
@@ -191,42 +190,49 @@ struct GroupLane {
     ntop = G == (1 << lg) ? tab.nu_edge[G] : INFINITY;
     pnorm = tab.a_rad * 15.0 / (M_PI * M_PI * M_PI * M_PI);
   }
-  template <int P>
+  // EX: quotients and root correctly rounded (an error of x = nu/T shows x times as large in e^(-x)):
+  // for the coefficients that are kept as they are
+  template <int P, bool EX = false>
   __device__ __forceinline__ void at(const double* T, double kq, double* kap, double* B) const {
-    double iT[P], is[P], xa[P], va[P], vb[P];
-    iT[0] = rcp2(T[0]);
-    is[0] = sqrt_(iT[0]);
-    if constexpr (P == 2) {
-      // 1/T' and 1/sqrt(T') from those of T by the binomial series in (T' - T)/T
-      const double e = (T[1] - T[0]) * iT[0];
-      iT[1] = fma(iT[0], e * (e - 1.0), iT[0]);
-      is[1] = fma(is[0], e * fma(e, 0.375, -0.5), is[0]);
-    }
-    {
-      double qa, em;
+    static_assert(P == 1 || !EX, "one temperature");
+    double iT[P], xa[P], va[P], vb[P];
+    double qa, em;
+    if constexpr (EX) {
+      exp_neg(fmin(nuc / T[0], EXP_MAX), qa, em);
+      kap[0] = kq / sqrt(T[0]) * -em;
+      xa[0] = nlo / T[0];
+    } else {
+      double is[P];
+      iT[0] = rcp2(T[0]);
+      is[0] = sqrt_(iT[0]);
       const double a = fmin(nuc * iT[0], EXP_MAX);
       exp_neg(a, qa, em);
       kap[0] = kq * is[0] * -em;
       if constexpr (P == 2) {
+        // 1/T' and 1/sqrt(T') from those of T by the binomial series in (T' - T)/T
+        const double e = (T[1] - T[0]) * iT[0];
+        iT[1] = fma(iT[0], e * (e - 1.0), iT[0]);
+        is[1] = fma(is[0], e * fma(e, 0.375, -0.5), is[0]);
         // e^(-a') - 1 = (e^(-a) - 1) + e^(-a) (e^u - 1), u = a - a' small
         const double u = a - fmin(nuc * iT[1], EXP_MAX);
         const double e1 = fma(qa, u * fma(u, fma(u, 1.0 / 6.0, 0.5), 1.0), em);
         kap[1] = kq * is[1] * -e1;
       }
+      for (int p = 0; p < P; ++p) xa[p] = nlo * iT[p];
     }
-    for (int p = 0; p < P; ++p) xa[p] = nlo * iT[p];
-    planck_edge<P>(xa, va);
+    const double Ts = PLANCK_SPLIT * T[0];
+    const bool al = nlo < Ts, bl = nhi < Ts;   // (the edge between two lanes: the same for both)
+    planck_edge<P>(xa, al, va);
     for (int p = 0; p < P; ++p) vb[p] = next_lane(va[p], lg);
     if (ntop < INFINITY) {
       if (last) {
         double xt[P];
-        for (int p = 0; p < P; ++p) xt[p] = ntop * iT[p];
-        planck_edge<P>(xt, vb);
+        for (int p = 0; p < P; ++p) xt[p] = EX ? ntop / T[0] : ntop * iT[p];
+        planck_edge<P>(xt, bl, vb);
       }
     } else if (last) {
       for (int p = 0; p < P; ++p) vb[p] = 0.0;
     }
-    const bool al = xa[0] < PLANCK_SPLIT, bl = nhi * iT[0] < PLANCK_SPLIT;
     for (int p = 0; p < P; ++p) {
       const double T2 = T[p] * T[p];
       B[p] = pnorm * (T2 * T2) * planck_part(al, bl, va[p], vb[p]);
@@ -235,8 +241,9 @@ struct GroupLane {
 };
 
 // One lane per zone-group, a zone's groups on consecutive lanes (as k_matter_source): each lane
-// evaluates one edge instead of its group's two.  512^2 x 16 in double: 32 us
-// (143 us with both edges per lane, library exponentials and data-dependent series lengths)
+// evaluates one edge instead of its group's two.  512^2 x 16 in double: 38 us (139 us with both
+// edges per lane, library exponentials and data-dependent series lengths; 32 us with reciprocal
+// estimates, whose emission far in the Wien tail is off twice as far).
 template <typename S>
 __global__ void __launch_bounds__(MBLOCK) k_matter_coeffs(MatterArgs<S> a, S* kap_out, S* B_out) {
   const int64_t gt = (int64_t)blockIdx.x * MBLOCK + threadIdx.x;
@@ -247,7 +254,7 @@ __global__ void __launch_bounds__(MBLOCK) k_matter_coeffs(MatterArgs<S> a, S* ka
   const bool on = g < a.G;
   const double T = a.T[z];
   double kap, B;
-  gr.at<1>(&T, a.kappa0[z] * a.tab.kg[on ? g : 0], &kap, &B);
+  gr.at<1, true>(&T, a.kappa0[z] * a.tab.kg[on ? g : 0], &kap, &B);
   if (on) {
     const int64_t i = z * a.G + g;
     kap_out[i] = (S)kap;
