@@ -521,6 +521,7 @@ int fornax_m1_create(const fornax_m1_desc* desc, fornax_m1_ctx** out) {
   }
   ctx->nb_partials =
       (size_t)std::max(std::max(ctx->rows.nblocks, ctx->c3.nblocks), std::max(ctx->tile_v1.nblocks, ctx->tile.nblocks));
+  ctx->nb_entries = nb;
   ctx->p_energy = (double*)red;
   ctx->p_maxf2 = ctx->p_energy + nb;
   ctx->p_nun = (int*)(ctx->p_maxf2 + nb);

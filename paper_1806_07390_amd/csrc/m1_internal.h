@@ -211,6 +211,7 @@ struct fornax_m1_ctx {
   // reduction scratch (one partial per block of the step kernel)
   int nblocks_step;
   size_t nb_partials;          // partials the step kernels may write (the most blocks of any)
+  size_t nb_entries;           // partials the scratch has room for
   double* p_energy;
   double* p_maxf2;
   int* p_nun;

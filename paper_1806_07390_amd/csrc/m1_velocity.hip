@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "m1_device.h"
+#include "m1_grid.h"
 #include "m1_internal.h"
 #include "m1_step.h"
 
@@ -528,7 +529,9 @@ int launch_vel_nd(fornax_m1_ctx* ctx, const Geo<R>& geo, StepArgs<S>& a, const V
   const bool want = diag && (diag->energy_total || diag->max_f || diag->n_unrealizable || diag->n_nonpositive);
   b.dEm = diag ? diag->dE_matter : nullptr;
   const int64_t need = (a.nzones + a.zones_per_block - 1) / a.zones_per_block;
-  int nb = (int)std::max<int64_t>(1, std::min<int64_t>(need, std::min<int64_t>(ctx->nb_partials, 65536)));
+  // 6 blocks per CU at least (MIXED 384 x 384 x 24 207 -> 188 us against the step tiling's 728
+  // blocks, 256 x 256 x 24 101 -> 93; more bring nothing there)
+  int nb = (int)std::min<int64_t>(stride_blocks(need, ctx->nb_partials, ctx->nb_entries, 6, ctx->cus), 65536);
   b.p_energy = ctx->p_energy;
   b.p_maxf2 = ctx->p_maxf2;
   b.p_nun = ctx->p_nun;

@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "m1_device.h"
+#include "m1_grid.h"
 #include "m1_internal.h"
 #include "m1_lane.h"
 #include "m1_step.h"
@@ -359,10 +360,14 @@ int launch_vel_freq_wave(const fornax_m1_ctx* ctx, const StepArgs<double>& b, co
                          int want, hipStream_t st) {
   const int64_t zpb = (int64_t)(64 / b.G) * (BLOCK / 64);
   const int64_t slots = 64 * (int64_t)(ctx->cus > 0 ? ctx->cus : 256);
-  const int nb = (int)std::max<int64_t>(
-      1, std::min<int64_t>(std::min<int64_t>((b.nzones + zpb - 1) / zpb, slots), (int64_t)ctx->nb_partials));
-  *nblocks = nb;
   const bool sph = ctx->desc.coord == FORNAX_SPHERICAL_LOGR;
+  // as many blocks per CU at least as the registers hold: 4, on spherical 3-D grids 3 (384 x 384 x 24
+  // 315 -> 305 us against the step tiling's blocks, 256 x 256 x 24 142 -> 135; 4 on the spherical
+  // 96 x 32 x 48 x 12 leave a round of blocks a third full: this kernel 51 -> 62 us)
+  const int64_t need = std::min<int64_t>((b.nzones + zpb - 1) / zpb, slots);
+  const int nb = (int)stride_blocks(need, ctx->nb_partials, ctx->nb_entries, sph && ctx->desc.ndim == 3 ? 3 : 4,
+                                    ctx->cus);
+  *nblocks = nb;
   const int shape = ctx->desc.ndim * 2 + (sph ? 1 : 0);
   if (va.Fn[0])   // 3-D grids only
     return sph ? launch_freq<true, 3, true>(b, ctx->geo_d, va, nb, want, st)
