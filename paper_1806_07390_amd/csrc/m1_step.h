@@ -36,6 +36,8 @@ int launch_rows(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, hip
 // inner radius and polar axes over a periodic phi of even length; NR 6, 8 or 12 in double,
 // 4, 8 or 16 in float, 8 (double) or 4, 8 and 12 (float) on spherical grids).
 C3Tile make_c3_tile(const fornax_m1_desc& D, int NR, int TM);
+// whether the grid's steps are faster there than with the tiled kernel's tile
+bool c3_pays(const fornax_m1_desc& D, const C3Tile& c3, const Tile& tiled, int cus);
 // the step's tiling, and Step 1 of the velocity step's (planes per block from the CU count)
 C3Tile choose_c3_tile(const fornax_m1_desc& D, int cus);
 C3Tile choose_c3_vel_tile(const fornax_m1_desc& D, int cus);

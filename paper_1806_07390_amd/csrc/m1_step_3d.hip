@@ -56,6 +56,7 @@
 #include <type_traits>
 
 #include "m1_device.h"
+#include "m1_grid.h"
 #include "m1_internal.h"
 #include "m1_lane.h"
 #include "m1_step.h"
@@ -728,13 +729,18 @@ C3Tile choose_c3_tile(const fornax_m1_desc& D, int cus) {
   // double 2, float Cartesian 4, float spherical 3.
   const bool dbl = D.precision == FORNAX_FP64;
   const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
-  // Group counts that leave rows idle (5 groups: 3 of 8) still run 1.2 to 2.3 times faster here
-  // than on the tiled kernel in double (1, 2, 3, 5, 6, 7, 9 and 10 groups, Cartesian 90 x 70 x 60
-  // and 180 x 160 x 150, spherical 96 x 32 x 48 and 256 x 64 x 128).  In float they keep the tiled
-  // kernel (make_c3_tile refuses them), and its results bit for bit: it adds the three directions
-  // in another order, and the float roundings of a step show in its double diagnostics and steer
-  // the limiter of the next.
+  // Group counts that leave rows idle (5 groups: 3 of 8) run here in double where that is faster
+  // than on the tiled kernel (c3_pays).  In float they keep the tiled kernel (make_c3_tile refuses
+  // them), and its results bit for bit: it adds the three directions in another order, and the
+  // float roundings of a step show in its double diagnostics and steer the limiter of the next.
   return c3_tile_by_rounds(D, (sph && !dbl) ? 12 : 8, dbl ? 2 : (sph ? 3 : 4), cus);
+}
+
+bool c3_pays(const fornax_m1_desc& D, const C3Tile& c3, const Tile& tiled, int cus) {
+  if (c3.nblocks <= 0 || D.ngroups % 4 == 0 || tiled.nblocks <= 0) return true;
+  return plane_kernel_pays(c3.nblocks, c3.TM, tiled.nblocks, tiled.nthreads, tiled.TM, D.n[2],
+                           D.coord == FORNAX_SPHERICAL_LOGR, D.limiter == FORNAX_LIMITER_MINMOD,
+                           D.limiter == FORNAX_LIMITER_PPM, D.wavespeed == FORNAX_WAVESPEED_M1, cus);
 }
 
 // Step 1 of the velocity step: 8 rows at two waves per SIMD in double, 12 rows at three in
@@ -747,9 +753,14 @@ C3Tile choose_c3_vel_tile(const fornax_m1_desc& D, int cus) {
   // spherical grids, and group counts that leave rows idle, from the size on where the blocks
   // fill the chip; below it one thread per zone-group is faster (measured in double: spherical
   // 32 x 8 x 8 x 12 80 against 49 us, 64 x 16 x 24 x 6 105 against 99, 160 x 48 x 80 x 3 276 against
-  // 475; Cartesian 20^3 x 3 55 against 42, 40 x 30 x 30 x 3 72 against 71, 144^3 x 3 791 against 1608)
+  // 475; Cartesian 20^3 x 3 55 against 42, 40 x 30 x 30 x 3 72 against 71, 144^3 x 3 791 against 1608).
+  // Limiters other than minmod, whose instantiation spills registers, from twice the size on (whole
+  // step with MC: 20^3 x 17 86 against 62 us, 26^3 x 10 82 against 72, 200 x 100 x 4 x 3 56 against 74;
+  // spherical 64 x 32 x 32 x 4 152 against 124, 128 x 48 x 64 x 1 153 against 140, 64 x 24 x 32 x 12
+  // 172 against 216)
   const int64_t nzg = (int64_t)D.n[0] * D.n[1] * D.n[2] * D.ngroups;
-  if ((sph && nzg < (1 << 18)) || (D.ngroups % 4 != 0 && nzg < (1 << 17))) return C3Tile{};
+  const int other = D.limiter != FORNAX_LIMITER_MINMOD ? 1 : 0;
+  if ((sph && nzg < (1 << (18 + other))) || (D.ngroups % 4 != 0 && nzg < (1 << (17 + other)))) return C3Tile{};
   return c3_tile_by_rounds(D, dbl ? 8 : 12, dbl ? 2 : 3, cus);
 }
 
