@@ -652,6 +652,12 @@ __device__ __forceinline__ void geometric_source(const R P[9], const R h[3], con
                 G323 * P[5] * (h[2] * ih1));
 }
 
+// The exponent k of the exact scale 2^k that brings |E| into [1/2, 1) (2^600 where E = 0), for states
+// whose squares, or the products of two of them by which the largest f is found, could underflow:
+// |E| below 2^-200 in double (no float is that small).
+constexpr double DIAG_SMALL = 0x1p-200;
+__device__ __forceinline__ int diag_scale(double E) { return E != 0.0 ? -__builtin_amdgcn_frexp_exp(E) : 600; }
+
 // Implicit interaction update of one zone-group in double (eq:be_update with j = c kappa B and
 // F^{n+1} = F^- / (1 + c dt (kappa + sigma))), store, and the zone-group's diagnostics
 // contributions: V E^{n+1}, f^2 = (|F^|/cE)^2, realizability and positivity counts.  Returns
@@ -698,16 +704,17 @@ __device__ __forceinline__ double source_zone(const StepArgsBase& a, const Geo<R
       hd[0] = hd[1] = (double)gld(geo.hr, i + NG);
       hd[2] = hd[0] * (double)gld(geo.hs, j + NG);
     }
-    // |E| below 2^-400: the squares below could underflow; f and the counts are those of the
-    // state scaled by 2^600 (exact), in waves that hold such a zone only
-    double Es = E1d, sc = 1.0;
-    if (__builtin_amdgcn_ballot_w64(fabs(E1d) < 0x1p-400) && fabs(E1d) < 0x1p-400) {
-      sc = 0x1p600;
-      Es = E1d * sc;
+    // tiny states: f and the counts are those of the state scaled by a power of two
+    double Es = E1d;
+    int k = 0;
+    if (sizeof(S) == 8 && __builtin_amdgcn_ballot_w64(fabs(E1d) < DIAG_SMALL) && fabs(E1d) < DIAG_SMALL) {
+      k = diag_scale(E1d);
+      Es = ldexp(E1d, k);
     }
     double F2 = 0.0;
     for (int cc = 0; cc < ND; ++cc) {
-      const double fk = (SPH ? F1s[cc] * rcp_(hd[cc]) : F1s[cc]) * sc;
+      double fk = SPH ? F1s[cc] * rcp_(hd[cc]) : F1s[cc];
+      if (sizeof(S) == 8) fk = ldexp(fk, k);
       F2 += fk * fk;
     }
     const double cE = c * Es;

@@ -143,13 +143,17 @@ __device__ __forceinline__ void wave_diag_count(double c, double E1, const doubl
                                                 WaveDiag& wd) {
   double Es = E1, F2 = 0.0;
   for (int k = 0; k < ND; ++k) F2 += F1[k] * F1[k];
-  // |E| below 2^-400: the squares could underflow; f and the counts are those of the state
-  // scaled by 2^600 (exact), in waves that hold such a zone only
-  if (__builtin_amdgcn_ballot_w64(fabs(E1) < 0x1p-400)) {
-    const double sc = fabs(E1) < 0x1p-400 ? 0x1p600 : 1.0;
-    Es = E1 * sc;
+  // tiny states: f and the counts are those of the state scaled by a power of two, in waves that
+  // hold such a zone only
+  if (sizeof(S) == 8 && (__builtin_amdgcn_ballot_w64(fabs(E1) < DIAG_SMALL) & upd)) {
+    __asm__ volatile("");
+    const int k2 = fabs(E1) < DIAG_SMALL ? diag_scale(E1) : 0;
+    Es = ldexp(E1, k2);
     F2 = 0.0;
-    for (int k = 0; k < ND; ++k) F2 += (F1[k] * sc) * (F1[k] * sc);
+    for (int k = 0; k < ND; ++k) {
+      const double fk = ldexp(F1[k], k2);
+      F2 += fk * fk;
+    }
   }
   const double cE = c * Es, cE2 = cE * cE;
   const bool up = Es > 0.0 && F2 * wd.fden > wd.fnum * cE2;
