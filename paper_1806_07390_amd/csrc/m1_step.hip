@@ -529,14 +529,15 @@ k_step_tiled(StepArgs<S> a, Geo<R> geo, Tile tl) {
     else return epsilon_uniform(ksL, ksR, R(0.5) * geo.dx[d]);
   };
   int dz_zone = -1;
-  // second Runge-Kutta stage, U^n of the plane's zones: loaded ahead of the plane's work (EA), all
-  // components together at the update in the double kernel that is held to a register budget (EB;
-  // 512 x 512 x 16 PPM RK2 262 -> 243 us against a load and a wait per component, 268 ahead) and on
-  // spherical 3-D grids in double (256 x 64 x 64 x 5 PPM RK2 3264 -> 3125), each at its use elsewhere:
-  // in the float kernel of that budget any other place spills registers (MIXED blobs 67 -> 69 us),
-  // and in 3-D the values held cost every launch, a second stage or not (Euler steps, ahead / at
-  // use: MIXED 100 x 80 x 60 x 6 171 / 162 us, double 180 x 160 x 8 x 5 MC 196 / 142)
-  constexpr bool EA = DIM < 3 && !(GBC > 0 && !SPH && V == 1);
+  // second Runge-Kutta stage, U^n of the plane's zones: in 2-D in double loaded ahead of the plane's
+  // work (EA), all components together at the update in the double kernel that is held to a
+  // register budget (EB; 512 x 512 x 16 PPM RK2 262 -> 243 us against a load and a wait per component,
+  // 268 ahead), in 1-D and on spherical 3-D grids in double (256 x 64 x 64 x 5 PPM RK2 3264 -> 3125),
+  // each at its use elsewhere: in the float kernel of that budget any other place spills registers
+  // (MIXED blobs 67 -> 69 us), in its other kernels and in 3-D the values held cost more than the
+  // waits (ahead / at use: MIXED 1500 x 700 x 9 RK2 536 / 500 us, and Euler steps, whose launches hold
+  // the registers too: MIXED 100 x 80 x 60 x 6 171 / 162, double 180 x 160 x 8 x 5 MC 196 / 142)
+  constexpr bool EA = DIM == 2 && sizeof(R) == 8 && !(GBC > 0 && !SPH && V == 1);
   constexpr bool EB = !EA && sizeof(R) == 8 && (DIM < 3 || SPH);
   const int pq = (tl.TM + 3) / 4;
   for (int m = mbeg; m < mend; ++m) {
