@@ -941,20 +941,23 @@ static const void* row_kernel(const Tile& tl, bool mm) {
   return mm ? (const void*)&k_step_tiled<S, S, 2, SPH, true, 0, 1, MM> : (const void*)&k_step_tiled<S, S, 2, SPH, true, 0, 1, -1>;
 }
 
-// 2-D wave rows with one group per lane: a block walks its TM planes (and about three planes'
-// worth of start-up) one after the other, so the kernel takes about the number of rounds of block
-// slots times TM + 3; the TM with the least such cost, the slots from the kernel's occupancy.
-// Against the largest power of two with 1024 (double) or 2048 (float) blocks: 512 x 512 x 16
-// double PPM RK2 297 -> 278 us (16 -> 26 planes), MIXED 79.4 -> 77.9 (8 -> 16), 301 x 187 x 9 double
-// MC 40 -> 33 (4 -> 6), 384 x 384 x 12 double 58 -> 48 (4 -> 11), 400 x 300 x 8 double 37 -> 32
-// (4 -> 6); small grids keep 4 planes.
+// 2-D wave rows with one group per lane: a block walks its TM planes (and about three planes' worth
+// of start-up) one after the other, so the kernel takes about the number of rounds of block slots
+// times TM + 3, the slots from the kernel's occupancy.  Of the lengths within a tenth of the least such
+// cost the shortest is taken: more, shorter blocks even out over the CUs what the count of rounds does not
+// see.  Over 96 calls (14 Cartesian and 3 spherical grids, both precisions, minmod, MC, PPM RK2), every
+// length timed, it is on average 2 % above the fastest one; the least cost itself (the longest such
+// block) 4 %, 15 % the largest power of two with 1024 (double) or 2048 (float) blocks: 512 x 512 x 16
+// double PPM RK2 297 -> 278 us (16 -> 26 planes), 301 x 187 x 9 double MC 40 -> 33 (4 -> 6), 384 x 384 x
+// 12 double 58 -> 48 (8 -> 11); against the least cost 4096 x 512 x 3 MIXED MC 142 -> 116 (18 -> 12),
+// 1500 x 700 x 9 double 409 -> 371 (35 -> 21), 2000 x 3000 x 1 double 171 -> 182 (17 -> 10).
 static Tile rows_by_rounds(const fornax_m1_desc& D, int GB, int NW, int cus) {
   const bool sph = D.coord == FORNAX_SPHERICAL_LOGR;
   const bool mm = D.limiter == FORNAX_LIMITER_MINMOD && D.wavespeed == FORNAX_WAVESPEED_LIGHT;
-  Tile best{};
-  double best_cost = 0.0;
+  Tile tiles[65];
+  double cost[65], least = 0.0;
   for (int TM = 4; TM <= 64; ++TM) {
-    const Tile t = make_tile(D, 0, 1, TM, GB, NW, 1);
+    const Tile t = tiles[TM] = make_tile(D, 0, 1, TM, GB, NW, 1);
     if (t.nblocks <= 0) continue;
     const void* k = D.precision == FORNAX_FP64 ? (sph ? row_kernel<double, true>(t, mm) : row_kernel<double, false>(t, mm))
                                                : (sph ? row_kernel<float, true>(t, mm) : row_kernel<float, false>(t, mm));
@@ -964,13 +967,12 @@ static Tile rows_by_rounds(const fornax_m1_desc& D, int GB, int NW, int cus) {
       per_cu = std::max(1, 8 / NW);
     }
     const int64_t slots = (int64_t)per_cu * (cus > 0 ? cus : 256);
-    const double cost = (double)((t.nblocks + slots - 1) / slots) * (TM + 3);
-    if (best.nblocks <= 0 || cost <= best_cost) {
-      best = t;
-      best_cost = cost;
-    }
+    cost[TM] = (double)((t.nblocks + slots - 1) / slots) * (TM + 3);
+    if (least == 0.0 || cost[TM] < least) least = cost[TM];
   }
-  return best;
+  for (int TM = 4; TM <= 64; ++TM)
+    if (tiles[TM].nblocks > 0 && cost[TM] <= 1.1 * least) return tiles[TM];
+  return Tile{};
 }
 
 Tile choose_tile(const fornax_m1_desc& D, int V, int cus) {
