@@ -466,6 +466,7 @@ int fornax_m1_create(const fornax_m1_desc* desc, fornax_m1_ctx** out) {
     if (ctx->tile.nblocks <= 0) ctx->tile = choose_tile(*desc, 1, cus);
     ctx->tile_v1 = (ctx->tile.V == 1) ? ctx->tile : choose_tile(*desc, 1, cus);
   }
+  const Tile chosen = ctx->tile;
   if (const char* env = std::getenv("FORNAX_M1_TILE")) {
     // "TXB,TYB,TM,GB[,NW[,V]]" (TXB, TYB ignored for 1-D/2-D wave rows, where TXB = 64 V/GB)
     int tx = 0, ty = 0, tm = 0, gbk = desc->ngroups, nw = 1, vv = 1;
@@ -502,6 +503,17 @@ int fornax_m1_create(const fornax_m1_desc* desc, fornax_m1_ctx** out) {
     (void)hipFree(ctx->geo_mem);
     delete ctx;
     return FORNAX_EUNSUPPORTED;
+  }
+  // where the partials of many short blocks, and nothing else, would push a 2-D step out of the static
+  // scratch of fornax_m1_step_noalloc: fewer blocks
+  if (desc->ndim == 2 && ctx->tile.nblocks == chosen.nblocks) {
+    const Tile few = few_blocks_tile(*desc);
+    auto fits = [&](const Tile& t, bool dem) {
+      return noalloc_layout(*desc, (size_t)std::max(ctx->rows.nblocks, t.nblocks), (size_t)t.ngb, dem).bytes <=
+             (size_t)FORNAX_M1_NOALLOC_SCRATCH_BYTES;
+    };
+    for (const bool dem : {false, true})
+      if (few.nblocks > 0 && !fits(ctx->tile, dem) && fits(few, dem)) ctx->tile = ctx->tile_v1 = few;
   }
   // reduction scratch: one partial per block of the step kernel, and per block of the
   // zone-block kernels (source)

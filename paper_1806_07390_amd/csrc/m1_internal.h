@@ -247,6 +247,26 @@ struct StepScratch {
   void* stage;
 };
 
+// Layout of the scratch of fornax_m1_step_noalloc: the partials of every block the step kernels may
+// launch (nb), the dE_matter partials of ngb split group blocks (when dE_matter is asked for), the
+// Runge-Kutta stage; each part 256-byte aligned.
+struct NoallocLayout {
+  size_t energy, maxf2, nun, nnp, dzp, stage, bytes;
+};
+inline NoallocLayout noalloc_layout(const fornax_m1_desc& D, size_t nb, size_t ngb, bool dem) {
+  const size_t nz = (size_t)D.n[0] * D.n[1] * D.n[2];
+  const size_t es = D.precision == FORNAX_FP64 ? sizeof(double) : sizeof(float);
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  NoallocLayout L{};
+  L.maxf2 = L.energy + al(nb * sizeof(double));
+  L.nun = L.maxf2 + al(nb * sizeof(double));
+  L.nnp = L.nun + al(nb * sizeof(int));
+  L.dzp = L.nnp + al(nb * sizeof(int));
+  L.stage = L.dzp + (dem && ngb > 1 ? al(ngb * nz * sizeof(double)) : 0);
+  L.bytes = L.stage + (D.integrator == FORNAX_SSPRK2 ? al((size_t)(1 + D.ndim) * nz * D.ngroups * es) : 0);
+  return L;
+}
+
 // kernel launchers (m1_kernels.hip)
 int fm1_launch_step(fornax_m1_ctx* ctx, const fornax_m1_state* in, fornax_m1_state* out,
                     const fornax_m1_coeffs* cf, const double* inflow, double dt,

@@ -13,6 +13,9 @@ namespace fm1 {
 // LDS budget).
 Tile make_tile(const fornax_m1_desc& D, int TXB, int TYB, int TM, int GB, int NW, int V);
 Tile choose_tile(const fornax_m1_desc& D, int V, int cus);
+// 2-D tiles of one group per lane with the largest power of two of planes (32 to 4) that leaves 1024
+// (double) or 2048 (float) blocks
+Tile few_blocks_tile(const fornax_m1_desc& D);
 // Raise the dynamic LDS limit of every step-kernel instantiation (once per process).
 int prepare_step_kernels();
 

@@ -928,9 +928,8 @@ Tile make_tile(const fornax_m1_desc& D, int TXB, int TYB, int TM, int GB, int NW
 }
 
 // Default tile.
-//  * 1-D / 2-D wave rows: with V = 2 (G even) each lane takes a pair of groups and GB = the
-//    largest power of two up to 8 dividing G, so that a wave row of 16 columns reads runs of
-//    8 groups; with V = 1, GB up to 4.  All G / GB group subsets of a tile share a block when
+//  * 1-D / 2-D wave rows: one group per lane (V = 1; pairs by the FORNAX_M1_TILE override only), GB = the
+//    largest power of two up to 4 dividing G.  All G / GB group subsets of a tile share a block when
 //    they fit in 8 waves.  Planes per block (2-D): see rows_by_rounds.
 //  * 3-D: a near-square tile of 128-512 threads; with many groups per zone, groups are split
 //    across blocks so that the zone tile stays large enough to amortise its halo.
@@ -975,15 +974,32 @@ static Tile rows_by_rounds(const fornax_m1_desc& D, int GB, int NW, int cus) {
   return Tile{};
 }
 
+// groups per wave row (one per lane) and wave rows per block
+static void row_groups(int G, int& GB, int& NW) {
+  GB = 1;
+  while (GB < 4 && G % (2 * GB) == 0) GB *= 2;
+  NW = std::min(8, G / GB);
+  while ((G / GB) % NW != 0) --NW;
+}
+
+Tile few_blocks_tile(const fornax_m1_desc& D) {
+  int GB, NW;
+  row_groups(D.ngroups, GB, NW);
+  Tile t{};
+  for (int TM = 32; TM >= 4; TM /= 2) {
+    t = make_tile(D, 0, 1, TM, GB, NW, 1);
+    if (t.nblocks >= (D.precision == FORNAX_FP64 ? 1024 : 2048)) break;
+  }
+  return t;
+}
+
 Tile choose_tile(const fornax_m1_desc& D, int V, int cus) {
   const int G = D.ngroups;
-  if (V == 2 && G % 2 != 0) return Tile{};
+  if (V == 2 && (G % 2 != 0 || D.ndim < 3)) return Tile{};
   if (D.ndim < 3) {
-    int GB = V;
-    while (GB < 4 * V && G % (2 * GB) == 0) GB *= 2;
-    int NW = std::min(8, G / GB);
-    while ((G / GB) % NW != 0) --NW;
-    if (D.ndim == 1) return make_tile(D, 0, 1, 1, GB, NW, V);
+    int GB, NW;
+    row_groups(G, GB, NW);
+    if (D.ndim == 1) return make_tile(D, 0, 1, 1, GB, NW, 1);
     return rows_by_rounds(D, GB, NW, cus);
   }
   // measured on gfx950 (192^3 x 12 and 256 x 64 x 128 x 20): Cartesian FP64 8 x 8 columns of
