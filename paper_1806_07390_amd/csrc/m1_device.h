@@ -23,9 +23,13 @@ namespace fm1 {
 // 0 in the last (pq: a quarter of the planes).  Left at one priority the waves of a SIMD are
 // served oldest first: the blocks that started first run ahead and leave, and the last ones
 // end alone on a chip that is no longer full (wave lives of 39 to 91 us in one 94 us launch);
-// with the waves that lag served first they end together.  512 x 512 x 16: double 97 -> 91 us,
-// MIXED 78 -> 69, double PPM RK2 278 -> 263; the adjoint run of 256 x 256 x 16 MIXED 1340 -> 1261 (16
-// forward-and-back steps; 1293 without it in the adjoint kernel).
+// with the waves that lag served first they end together.  512 x 512 x 16: double 98.5 -> 92.8 us,
+// MIXED 60.7 -> 58.0, double PPM RK2 264 -> 248; an adjoint step of 512 x 512 x 16 MIXED 134.2 ->
+// 132.8.  Launches of several rounds of blocks, where a fresh block outranks one near its end, gain
+// less and lose nothing: 1024 x 1024 x 16 double 340 -> 336, MIXED 235 -> 228; 2048 x 2048 x 8 double
+// 754 -> 756, MIXED 435 -> 423.  Over 166 grids, options and types 1 % faster in the geometric mean;
+// slower where a round's last blocks are few: 256 x 256 x 24 MIXED 41.2 -> 43.8, 1500 x 700 x 9 and
+// 4096 x 512 x 3 MIXED PPM RK2 472 -> 487 and 279 -> 289.
 __device__ __forceinline__ void prio_by_progress(int done, int pq) {
   if (done < pq) __builtin_amdgcn_s_setprio(3);
   else if (done < 2 * pq) __builtin_amdgcn_s_setprio(2);

@@ -241,8 +241,8 @@ struct GroupLane {
 };
 
 // One lane per zone-group, a zone's groups on consecutive lanes (as k_matter_source): each lane
-// evaluates one edge instead of its group's two.  512^2 x 16 in double: 38 us (139 us with both
-// edges per lane, library exponentials and data-dependent series lengths; 32 us with reciprocal
+// evaluates one edge instead of its group's two.  512^2 x 16 in double: 39 us (145 us with both
+// edges per lane, library exponentials and data-dependent series lengths; 34 us with reciprocal
 // estimates, whose emission far in the Wien tail is off twice as far).
 template <typename S>
 __global__ void __launch_bounds__(MBLOCK) k_matter_coeffs(MatterArgs<S> a, S* kap_out, S* B_out) {
@@ -266,7 +266,7 @@ __global__ void __launch_bounds__(MBLOCK) k_matter_coeffs(MatterArgs<S> a, S* ka
 // take a tenth of its time), so the work per residual is what counts: the residual and its
 // forward-difference neighbour are evaluated together (every accepted temperature needs both),
 // sharing the exponentials, and the group sums are lane permutations instead of LDS round
-// trips.  512^2 x 16 in double, 3.1 iterations in the slowest zone of a wave: 242 us (821 us with
+// trips.  512^2 x 16 in double, 3.1 iterations in the slowest zone of a wave: 211 us (767 us with
 // separate residuals, library exponentials and series of data-dependent length); VALU issue about
 // 60 % of the cycles at five waves per SIMD.
 template <typename S>

@@ -1,5 +1,6 @@
-// m1_step_3d.hip -- the fused M1 step for 3-D grids: the Cartesian 192^3 x 12 workload's layout, and spherical (ln r, theta, phi) grids with an inflow
-// inner boundary, polar axes and periodic phi (the 256 x 64 x 128 x 20 workload).
+// m1_step_3d.hip -- the fused M1 step for 3-D grids: Cartesian ones (the 192^3 x 12 workload's
+// layout), and spherical (ln r, theta, phi) grids with an inflow inner boundary, polar axes and
+// periodic phi (the 256 x 64 x 128 x 20 workload).
 //
 // Same method and arithmetic as k_step_tiled (eq:finite_vol with the reconstruction of
 // eq:recon_constraints, the M1 closure, the HLL flux eq:hll with the correction eq:epsilon, the
@@ -32,12 +33,13 @@
 // What the plane loop waits for is kept out of it by hand: values loaded a plane ahead are moved
 // into registers of their own where they are consumed, so that no copy of a load in flight
 // (with a wait for it) falls before the barrier, every outer-row item is loaded without a branch,
-// and addresses are a uniform base plus a 32-bit lane offset.  192^3 x 12 FP64 3626 -> 3505 us,
-// MIXED 2332 -> 2236 us, 256 x 64 x 128 x 20 MIXED (f mostly above 0.9) 2400 -> 2205 us with the
-// closure's new double form.  Stamps taken inside the loop show where the rest goes in double:
+// and addresses are a uniform base plus a 32-bit lane offset.  With this and the closure's form in
+// the squares of f, whole steps with diagnostics: 192^3 x 12 FP64 3681 -> 3546 us, MIXED 2214 ->
+// 2142, 256 x 64 x 128 x 20 MIXED (f mostly above 0.9) 2368 -> 2159.
+// Stamps taken inside the loop show where the rest goes in double:
 // of the two waves on a SIMD the older takes a plane in 6800 cycles and waits 3900 at the barrier
 // for the younger one; VALU issue 62 %.
-// With VEL (Cartesian grids), Step 1 of the velocity step: the same transport without the
+// With VEL (Cartesian grids, in double spherical ones too), Step 1 of the velocity step: the same transport without the
 // interaction update, each face flux with the advective flux v^d U of the upwind face state
 // added (the face's left state where v^d >= 0), from the normal velocity component on the face;
 // the zone-local velocity terms of the flux rows follow in the frequency step.
@@ -45,10 +47,10 @@
 // per-axis tables (volume-coordinate slopes, face scale factors for the realizability checks and
 // the fluxes, face weights and zone widths for the divergence, proper widths for the optical
 // depth; the radial values of the block's columns staged in LDS once, the theta values of the
-// wave's row read by scalar loads), the geometric source terms after the divergence, theta faces on the polar axis
-// closed; a polar-axis ghost row takes the mirrored row of the plane n_phi/2 away (with F_theta
-// and F_phi flipped), and an inflow ghost column the prescribed state with its own scale
-// factors.
+// wave's row read by scalar loads), the geometric source terms after the divergence, theta faces
+// on the polar axis closed; a polar-axis ghost row takes the mirrored row of the plane n_phi/2
+// away (with F_theta and F_phi flipped), and an inflow ghost column the prescribed state with its
+// own scale factors.
 
 #include <hip/hip_runtime.h>
 
@@ -282,8 +284,8 @@ k_step_3d(StepArgs<S> a, Geo<S> geo, C3Tile tl, VelArgs<S> va) {
   R k0, s0;
   // values in flight: q(m + 2), the outer x neighbour (columns 0, 15) of plane m and the
   // wave's outer-row items of plane m, kappa, sigma of m + 1 (Pk, Ps) and B of m (PB), all
-  // loaded at the top of the plane before (Pk2, Ps2, PB2: those of the next plane)
-  R Pr[4], Po[4], Ph[NHI], Pk, Ps, PB, Pk2, Ps2, PB2;
+  // loaded at the top of the plane before
+  R Pr[4], Po[4], Ph[NHI], Pk, Ps, PB;
   unsigned y0m, y1m, y2m, y3m;   // F_z sign masks of planes m .. m + 3 (the lane's own row)
   int64_t p1, p2, p3;            // element offsets of planes m + 1, m + 2, m + 3
   FaceAux<R> xM{};               // |F^|^2 and cE of hiM
@@ -770,6 +772,9 @@ int launch_c3(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, hipSt
   if (tl.nblocks <= 0) return FORNAX_EUNSUPPORTED;
   if (a.dEm && tl.ngb > 1 && !a.dzp) return FORNAX_EUNSUPPORTED;
   // the minmod instantiation has the -+c bounds built in; the other takes both options at run time
+  // and spills in double (24 registers on Cartesian grids, 98 on spherical ones; Step 1 of the
+  // velocity step 47 and 126): the rules for odd group counts and for Step 1 (plane_kernel_margin,
+  // choose_c3_vel_tile) have lines of their own for it
   const bool mm = a.limiter == FORNAX_LIMITER_MINMOD && a.wavespeed == FORNAX_WAVESPEED_LIGHT;
   const bool sph = ctx->desc.coord == FORNAX_SPHERICAL_LOGR;
   dim3 grid(tl.nblocks), block(64 * tl.NR);
@@ -813,8 +818,8 @@ template int launch_c3<double>(fornax_m1_ctx*, const Geo<double>&, const StepArg
 template int launch_c3<float>(fornax_m1_ctx*, const Geo<float>&, const StepArgs<float>&, hipStream_t);
 
 // Step 1 of the velocity step (transport with the advective fluxes, no interaction update, no
-// diagnostics) on 3-D Cartesian grids of the kernel's kind: 8-row blocks in double, 12-row
-// blocks (three waves per SIMD) in float, planes per block chosen at create.
+// diagnostics) on 3-D grids of the kernel's kind, in float Cartesian ones only: 8-row blocks in
+// double, 12-row blocks (three waves per SIMD) in float, planes per block chosen at create.
 template <typename S>
 int launch_c3_vel(fornax_m1_ctx* ctx, const Geo<S>& geo, const StepArgs<S>& a, const VelArgs<S>& va, hipStream_t st) {
   const fornax_m1_desc& D = ctx->desc;

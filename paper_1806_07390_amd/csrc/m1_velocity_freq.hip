@@ -7,11 +7,12 @@
 // them (SHARE; small group counts, with more zones per wave than 64 / ND^2, form them per lane).
 // Waves stride over the zones and carry their zone indices along, so no zone index is divided.
 //
-// Bound by memory: 192^3 zones x 12 groups in 3-D, 14 arrays in and out, 2.31 ms (4.4 TB/s; a plain
+// Bound by memory: 192^3 zones x 12 groups in 3-D, 14 arrays in and out, 2.08 ms (4.6 TB/s; a plain
 // kernel that reads 10 arrays and writes 4 of this size takes 1.8 ms with full aligned waves and
-// 1.95 with 60 of 64 lanes), against 2.95 ms for whole zones per block (k_vel_freq: 3 barriers per
+// 1.95 with 60 of 64 lanes), against 2.91 ms for whole zones per block (k_vel_freq: 3 barriers per
 // pass, 695 vector instructions against 440).  Loads of the next zones in flight across the pass,
-// 2 or 3 waves per SIMD, zones in one run per XCD, or non-temporal access: 2.27 to 2.64 ms.
+// 2 or 3 waves per SIMD, zones in one run per XCD, or non-temporal access: 2.27 to 2.64 ms, on a
+// card where this form took 2.31.
 //
 // The contractions of a zone are taken through the symmetric matrices S = W + W^T of the two sign
 // parts W of the gradient: with f = F^/(cE), P^^ = iso delta + ani f f and the third moment
